@@ -43,6 +43,7 @@ HBM_PEAK = 8e12
 # (nonzero apodization weight) count: the others add exactly zero to the sum.
 OPS_PER_GATHER, OPS_PER_PIX_CH, OPS_PER_PIX_ANGLE = 6, 9, 2
 KERNEL_SOURCES = ["paper_2311_00482_amd/csrc/beamform.hip",
+                  "paper_2311_00482_amd/csrc/beamform_kernels.h",
                   "paper_2311_00482_amd/csrc/beamform_device.h",
                   "paper_2311_00482_amd/csrc/plan.h"]
 COUNTERS = os.path.join(ROOT, "profiles", "k_beamform_c3_compound_f32.counters.json")

@@ -22,8 +22,8 @@ ROOT = os.path.dirname(HERE)
 ARCH = os.environ.get("PWBF_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["plan.cpp", "tune.cpp", "api.cpp", "batch.cpp", "serve.cpp", "serve_core.cpp", "metrics.cpp", "fk.cpp",
-           "beamform.hip",
-           "postz.hip", "batch.hip", "serve.hip", "iq.hip", "metrics.hip", "fk.hip",
+           "beamform.hip", "beamform_dmas.hip", "beamform_pdas.hip", "beamform_iqdas.hip",
+           "beamform_bbdmas.hip", "postz.hip", "batch.hip", "serve.hip", "iq.hip", "metrics.hip", "fk.hip",
            "noalloc.hip"]
 
 COMMON = [

@@ -288,7 +288,8 @@ __device__ __forceinline__ float ff_f(ff a) { return a.hi + a.lo; }
 template <bool B> struct Flag { static constexpr bool value = B; };
 
 // AM: angles handled per pixel; PRED: AM is an upper bound and angles >= A are
-// skipped (generic bucket), else exactly AM == A angles, fully unrolled.
+// skipped (17..32 angles of the IQ modes, batch and serving frames of other than
+// 1, 5 and 11 angles), else exactly AM == A angles, fully unrolled.
 // ONEGRP: one lane group per wavefront (cpw == 1), so the LDS window of a
 // channel is the same for the whole wavefront and its address stays scalar.
 // SEL: the apodization weight carries the aperture test (needed for boxcar).

@@ -1,0 +1,79 @@
+#pragma once
+// The single-frame beamform kernel and its launch for one beamformer: one block
+// per pixel tile. The tile body (staging, delays, gather, reductions) lives in
+// beamform_device.h; each beamformer's kernels are compiled in a source of their
+// own (beamform.hip, beamform_dmas.hip, ...).
+//
+// Tiles run deepest row first: a tile's cost grows with the receive aperture,
+// which widens with depth, so the costliest tiles start first and the cheap
+// shallow ones fill the end of the launch. Consecutive block ids go
+// round-robin to the 8 XCDs, so every XCD takes every 8th tile of each tile
+// row: an equal share of every depth.
+#include <hip/hip_runtime.h>
+
+#include "beamform_device.h"
+
+namespace pwbf {
+
+namespace {
+
+template <int AM, bool PRED, int MODE, bool ONEGRP>
+__global__ void __launch_bounds__(kWave * kMaxWavesPerBlock) k_beamform(const FramePlan P) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int b = blockIdx.x;
+  // RF modes: clear the frame maximum the post-processing folds into (the IQ
+  // modes fold it here, so their launch clears it beforehand)
+  if (!is_iq_mode(MODE) && P.ws_max && b == 0) dev::frame_max_clear(P.ws_max, threadIdx.x);
+  const int q = b / P.tiles_x;
+  const int tz = P.tiles_z - 1 - q, tx = b - q * P.tiles_x;
+  dev::process_tile<AM, PRED, MODE, ONEGRP>(P, tz, tx, smem);
+}
+
+template <int AM, bool PRED, int MODE>
+hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
+  const dim3 block(kWave * P.wz * P.wx);
+  const dim3 grid(P.n_tiles);
+  const size_t lds = plan_lds_bytes(P);
+  if (P.cpw == 1)
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, true>), grid, block, lds, stream, P);
+  else
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, false>), grid, block, lds, stream, P);
+  return hipGetLastError();
+}
+
+// An exactly unrolled kernel for every angle count, except 17..32 angles of the
+// IQ modes (two sums and a transmit delay per angle stay in registers: 96 of
+// them at 32 angles), which share a predicated one. A kernel that tests each
+// angle against the count takes the angles of a channel one LDS round trip
+// after another instead of all at once: a 21-angle DAS frame of 96 channels and
+// 301 x 777 pixels takes 238 us with it and 101 us unrolled, a 7-angle BB-DMAS
+// frame of 64 channels and 384 x 500 pixels 102 and 67 us (demodulation and log
+// image included).
+template <int MODE>
+hipError_t launch_mode(const FramePlan &P, hipStream_t stream) {
+  switch (P.n_angles) {
+#define PWBF_CASE(n) \
+  case n: return launch_angles<n, false, MODE>(P, stream);
+    PWBF_CASE(1) PWBF_CASE(2) PWBF_CASE(3) PWBF_CASE(4) PWBF_CASE(5) PWBF_CASE(6) PWBF_CASE(7)
+    PWBF_CASE(8) PWBF_CASE(9) PWBF_CASE(10) PWBF_CASE(11) PWBF_CASE(12) PWBF_CASE(13)
+    PWBF_CASE(14) PWBF_CASE(15) PWBF_CASE(16)
+    default: break;
+  }
+  if constexpr (is_iq_mode(MODE)) {
+    if (P.n_angles > 16 && P.n_angles <= kMaxAngles)
+      return launch_angles<kMaxAngles, true, MODE>(P, stream);
+  } else {
+    switch (P.n_angles) {
+      PWBF_CASE(17) PWBF_CASE(18) PWBF_CASE(19) PWBF_CASE(20) PWBF_CASE(21) PWBF_CASE(22)
+      PWBF_CASE(23) PWBF_CASE(24) PWBF_CASE(25) PWBF_CASE(26) PWBF_CASE(27) PWBF_CASE(28)
+      PWBF_CASE(29) PWBF_CASE(30) PWBF_CASE(31) PWBF_CASE(32)
+      default: break;
+    }
+  }
+#undef PWBF_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+}  // namespace pwbf
