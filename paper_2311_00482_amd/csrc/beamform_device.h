@@ -33,30 +33,55 @@
 namespace pwbf {
 namespace dev {
 
-// RF storage types: element size and a load through a raw buffer resource
-// (32-bit byte offset, scalar base), widened to float.
+// RF storage types: element size, one sample widened to float, and five
+// consecutive samples through wide loads, all through a raw buffer resource
+// (32-bit byte offset, scalar base):
+//   FP32: 16 + 4 bytes at the sample (dword-aligned);
+//   int16, FP16: the three dwords that hold the five samples, shifted by the
+//   half-word when the first sample lies in the upper one (element offset odd);
+//   they reach one sample past the five, and the record must be dword-aligned.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x3 __attribute__((ext_vector_type(3)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
 template <int DT>
-struct RfT;
-template <>
-struct RfT<kI16> {
-  static constexpr int kBytes = 2;
-  static __device__ __forceinline__ float load(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    return (float)(short)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
+struct RfT {  // kI16, kF16
+  static constexpr int kBytes = 2, kReach = 6;  // samples a wide load may touch
+  static __device__ __forceinline__ float widen(unsigned short h) {
+    if constexpr (DT == kF16) return __half2float(__ushort_as_half(h));
+    return (float)(short)h;
   }
-};
-template <>
-struct RfT<kF16> {
-  static constexpr int kBytes = 2;
   static __device__ __forceinline__ float load(__amdgpu_buffer_rsrc_t r, unsigned off) {
-    const unsigned short h = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
-    return __half2float(__ushort_as_half(h));
+    return widen((unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0));
+  }
+  static __device__ __forceinline__ void load5(__amdgpu_buffer_rsrc_t r, unsigned elem,
+                                               float (&u)[5]) {
+    const u32x3 w = __builtin_amdgcn_raw_buffer_load_b96(r, (int)((elem * 2u) & ~3u), 0, 0);
+    const unsigned sh = (elem & 1u) << 4;
+    const unsigned t0 = __builtin_amdgcn_alignbit(w.y, w.x, sh);
+    const unsigned t1 = __builtin_amdgcn_alignbit(w.z, w.y, sh);
+    u[0] = widen((unsigned short)t0);
+    u[1] = widen((unsigned short)(t0 >> 16));
+    u[2] = widen((unsigned short)t1);
+    u[3] = widen((unsigned short)(t1 >> 16));
+    u[4] = widen((unsigned short)(w.z >> sh));
   }
 };
 template <>
 struct RfT<kF32> {
-  static constexpr int kBytes = 4;
+  static constexpr int kBytes = 4, kReach = 5;
   static __device__ __forceinline__ float load(__amdgpu_buffer_rsrc_t r, unsigned off) {
     return __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  }
+  static __device__ __forceinline__ void load5(__amdgpu_buffer_rsrc_t r, unsigned elem,
+                                               float (&u)[5]) {
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(elem * 4u), 0, 0);
+    const unsigned b = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(elem * 4u + 16u), 0, 0);
+    u[0] = __uint_as_float(a.x);
+    u[1] = __uint_as_float(a.y);
+    u[2] = __uint_as_float(a.z);
+    u[3] = __uint_as_float(a.w);
+    u[4] = __uint_as_float(b);
   }
 };
 
@@ -64,27 +89,32 @@ struct RfT<kF32> {
 constexpr int kRawBufferWord3 = 0x00020000;
 
 // Stage the windows of a chunk: rows r = c A + a (channel e0 + c, angle a) of
-// win entries each (win a multiple of 4), described by the row table s_row:
-// {offset of the record of (angle, channel) in elements, first sample n0 of the
-// window}. Entry j of a row covers samples n = n0 + j and n + 1, i.e. kernel
-// delays s in [m, m + 1) with m = j - off, and holds, with du = u[n+1] - u[n],
+// win entries each (win a multiple of 4). Entry j of a row covers samples
+// n = n0 + j and n + 1, n0 = s_lt[a] + s_lr[c] the first sample of the window,
+// i.e. kernel delays s in [m, m + 1) with m = j - off, and holds, with
+// du = u[n+1] - u[n],
 //   DAS:  the line through both samples in s:  (u[n] - m du, du),
 //         so the interpolated value is b + s du (no fraction needed);
 //   DMAS: (u[n], du), interpolated as u[n] + frac(s) du, which keeps the
-//         rounding of v small where the signed square root is steep.
-// Samples outside [0, n_samples) read as zero (the table gives rows that must
-// be all zero a first sample far below 0).
+//         rounding of v small where the signed square root is steep;
+//   IQ:   the lines of the real and imaginary parts, (b_re, d_re, b_im, d_im).
+// Samples outside [0, n_samples) read as zero; rows of padding channels (past
+// the last one of the tile, several lane groups only) are all zero.
 //
-// Each thread fills 4 consecutive entries of a row from 5 consecutive samples,
-// read through one 32-bit buffer offset with immediate increments; where the 5
-// samples straddle an end of the record the reads are clamped into it and the
-// outside samples replaced by zero. Every read stays inside the RF buffer.
-//
+// Each thread fills 4 consecutive entries of a row from 5 consecutive samples.
 // Threads keep a fixed column of quads: with W4 = win / 4 quads per row and
 // R = blockDim / W4 >= 1, thread t stages quad t mod W4 of rows t / W4, + R,
 // + 2R, ..., so its entry offsets are set up once (the fewer than W4 threads
 // past R W4 stay idle). A window holds at most kMaxWindow = 64 entries (the
 // host refuses longer ones), so W4 <= 16 is never more than a wavefront.
+//
+// The five samples come through wide loads (one or two instructions instead of
+// five). Where those of some thread of the wavefront straddle an end of their
+// record, or the storage is not dword-aligned, all are read one by one, clamped
+// into the record, and the outside ones replaced by zero. Every read stays inside the RF buffer. (Two or
+// four quads of a thread loaded before the first is written were slower: 103 us
+// at two for the 11-angle 1024 x 1024 DAS frame against 101.5; the other blocks
+// of the CU gather meanwhile.)
 struct QuadWalk {
   int row0, drow, j0;
   bool active;
@@ -102,98 +132,126 @@ __device__ __forceinline__ QuadWalk quad_walk(int W4) {
   return w;
 }
 
-template <int DT, int MODE>
-__device__ __forceinline__ void stage_windows(const FramePlan &P, int rows, int off,
-                                              const int2 *s_row, float2 *s_pairs) {
+// The rows of a chunk as the staging threads address them.
+struct StageRows {
+  int rows, A;     // rows of the chunk, angles
+  int e0, e_hi;    // first channel of the chunk, end of the tile's channels
+  int off;         // off_t + off_r
+  const int *s_lt;  // [A] window origins of the angles
+  const int *s_lr;  // window origins of the chunk's channels
+};
+
+// Row r: the element offset of its record and its window's first sample.
+// r / A through a float reciprocal when A is not known at compile time
+// (r < 2^13: (r + 0.5) / A lies at least 1 / 64 from an integer).
+template <int AK>
+__device__ __forceinline__ int2 stage_row(const FramePlan &P, const StageRows &S, int r) {
+  int c;
+  if constexpr (AK > 0)
+    c = (int)((unsigned)r / (unsigned)AK);
+  else
+    c = (int)(((float)r + 0.5f) * __builtin_amdgcn_rcpf((float)S.A));
+  const int a = r - c * (AK > 0 ? AK : S.A);
+  const int e = S.e0 + c;
+  // the record offset is a full 32-bit product (n_samples may exceed the 24-bit
+  // multiplier's range; the host bounds the product below 2^31)
+  return make_int2((__mul24(a, P.n_channels) + min(e, P.n_channels - 1)) * P.n_samples,
+                   e < S.e_hi ? S.s_lt[a] + S.s_lr[c] : -(1 << 30));
+}
+
+template <int DT, int MODE, int AK>
+__device__ __forceinline__ void stage_windows(const FramePlan &P, const StageRows &S,
+                                              float2 *s_pairs) {
   using R = RfT<DT>;
   constexpr int B = R::kBytes;
   const int Ns = P.n_samples, win = P.win;
-  const unsigned lim = (unsigned)max(Ns - 4, 0);  // n in [0, lim): all 5 samples inside
+  // n in [0, lim): every sample that a wide load touches lies inside the record
+  const unsigned lim =
+      B == 4 || ((uintptr_t)P.rf & 3) == 0 ? (unsigned)max(Ns - R::kReach + 1, 0) : 0u;
   // the plan's angles only: A * N * Ns * B < 2^31 bytes (checked on the host)
   const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void *>(P.rf), (short)0, P.n_angles * P.n_channels * Ns * B, kRawBufferWord3);
   const QuadWalk w = quad_walk(win >> 2);
   if (!w.active) return;
-  {
-    const int j0 = w.j0;
-    const float m0 = (float)(off - j0);  // delay coordinate of entry j0
-    for (int row = w.row0; row < rows; row += w.drow) {
-      const int2 rb = s_row[row];
-      const int n = rb.y + j0;
-      float u[5];
-      if ((unsigned)n < lim) {
-        const unsigned vo = (unsigned)(rb.x + n) * B;
+  const int j0 = w.j0;
+  const float m0 = (float)(S.off - j0);  // delay coordinate of entry j0
+  for (int row = w.row0; row < S.rows; row += w.drow) {
+    const int2 rb = stage_row<AK>(P, S, row);
+    const int n = rb.y + j0;
+    float u[5];
+    if (__all((unsigned)n < lim)) {
+      R::load5(res, (unsigned)(rb.x + n), u);
+    } else {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) u[k] = R::load(res, vo + k * B);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const int i = n + k;
-          const float v = R::load(res, (unsigned)(rb.x + min(max(i, 0), Ns - 1)) * B);
-          u[k] = (unsigned)i < (unsigned)Ns ? v : 0.f;
-        }
+      for (int k = 0; k < 5; ++k) {
+        const int i = n + k;
+        const float v = R::load(res, (unsigned)(rb.x + min(max(i, 0), Ns - 1)) * B);
+        u[k] = (unsigned)i < (unsigned)Ns ? v : 0.f;
       }
-      float v8[8];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float du = u[k + 1] - u[k];
-        v8[2 * k] = MODE == kDas ? fmaf(m0 - (float)k, du, u[k]) : u[k];
-        v8[2 * k + 1] = du;
-      }
-      float4 *dst = (float4 *)(s_pairs + __mul24(row, win) + j0);
-      dst[0] = make_float4(v8[0], v8[1], v8[2], v8[3]);
-      dst[1] = make_float4(v8[4], v8[5], v8[6], v8[7]);
     }
+    float v8[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float du = u[k + 1] - u[k];
+      v8[2 * k] = MODE == kDas ? fmaf(m0 - (float)k, du, u[k]) : u[k];
+      v8[2 * k + 1] = du;
+    }
+    float4 *dst = (float4 *)(s_pairs + __mul24(row, win) + j0);
+    dst[0] = make_float4(v8[0], v8[1], v8[2], v8[3]);
+    dst[1] = make_float4(v8[4], v8[5], v8[6], v8[7]);
   }
 }
 
-// Stage the complex windows of the IQ modes: as stage_windows for DAS, with
-// each entry the lines of the real and imaginary parts, (b_re, d_re, b_im, d_im)
-// (16 bytes), from complex float32 samples.
-__device__ __forceinline__ void stage_windows_iq(const FramePlan &P, int rows, int off,
-                                                 const int2 *s_row, float4 *s_ent) {
+// The IQ modes' windows from complex float32 samples.
+template <int AK>
+__device__ __forceinline__ void stage_windows_iq(const FramePlan &P, const StageRows &S,
+                                                 float4 *s_ent) {
   const int Ns = P.n_samples, win = P.win;
-  const unsigned lim = (unsigned)max(Ns - 4, 0);
+  const unsigned lim = (unsigned)max(Ns - 4, 0);  // n in [0, lim): all 5 samples inside
   const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void *>(P.rf), (short)0, P.n_angles * P.n_channels * Ns * 8, kRawBufferWord3);
   const QuadWalk w = quad_walk(win >> 2);
   if (!w.active) return;
-  {
-    const int j0 = w.j0;
-    const float m0 = (float)(off - j0);
-    for (int row = w.row0; row < rows; row += w.drow) {
-      const int2 rb = s_row[row];
-      const int n = rb.y + j0;
-      float ur[5], ui[5];
-      if ((unsigned)n < lim) {
-        const unsigned vo = (unsigned)(rb.x + n) * 8u;
+  const int j0 = w.j0;
+  const float m0 = (float)(S.off - j0);
+  for (int row = w.row0; row < S.rows; row += w.drow) {
+    const int2 rb = stage_row<AK>(P, S, row);
+    const int n = rb.y + j0;
+    float ur[5], ui[5];
+    if (__all((unsigned)n < lim)) {
+      const int vo = (int)((unsigned)(rb.x + n) * 8u);
+      const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(res, vo, 0, 0);
+      const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(res, vo + 16, 0, 0);
+      const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(res, vo + 32, 0, 0);
+      ur[0] = __uint_as_float(a.x);
+      ui[0] = __uint_as_float(a.y);
+      ur[1] = __uint_as_float(a.z);
+      ui[1] = __uint_as_float(a.w);
+      ur[2] = __uint_as_float(b.x);
+      ui[2] = __uint_as_float(b.y);
+      ur[3] = __uint_as_float(b.z);
+      ui[3] = __uint_as_float(b.w);
+      ur[4] = __uint_as_float(c.x);
+      ui[4] = __uint_as_float(c.y);
+    } else {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          ur[k] = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)(vo + 8 * k), 0, 0));
-          ui[k] = __int_as_float(
-              (int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)(vo + 8 * k + 4), 0, 0));
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const int i = n + k;
-          const unsigned vo = (unsigned)(rb.x + min(max(i, 0), Ns - 1)) * 8u;
-          const float re =
-              __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)vo, 0, 0));
-          const float im =
-              __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(res, (int)(vo + 4u), 0, 0));
-          const bool in = (unsigned)i < (unsigned)Ns;
-          ur[k] = in ? re : 0.f;
-          ui[k] = in ? im : 0.f;
-        }
+      for (int k = 0; k < 5; ++k) {
+        const int i = n + k;
+        const int vo = (int)((unsigned)(rb.x + min(max(i, 0), Ns - 1)) * 8u);
+        const float re = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(res, vo, 0, 0));
+        const float im =
+            __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(res, vo + 4, 0, 0));
+        const bool in = (unsigned)i < (unsigned)Ns;
+        ur[k] = in ? re : 0.f;
+        ui[k] = in ? im : 0.f;
       }
-      float4 *dst = s_ent + __mul24(row, win) + j0;
+    }
+    float4 *dst = s_ent + __mul24(row, win) + j0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float m = m0 - (float)k;
-        const float dr = ur[k + 1] - ur[k], di = ui[k + 1] - ui[k];
-        dst[k] = make_float4(fmaf(m, dr, ur[k]), dr, fmaf(m, di, ui[k]), di);
-      }
+    for (int k = 0; k < 4; ++k) {
+      const float m = m0 - (float)k;
+      const float dr = ur[k + 1] - ur[k], di = ui[k + 1] - ui[k];
+      dst[k] = make_float4(fmaf(m, dr, ur[k]), dr, fmaf(m, di, ui[k]), di);
     }
   }
 }
@@ -284,6 +342,16 @@ __device__ __forceinline__ ff ff_sqrt(ff a) {
 }
 __device__ __forceinline__ float ff_f(ff a) { return a.hi + a.lo; }
 
+// A float that is the same in every lane, moved to a scalar register: computed by
+// the vector unit, it would hold a vector register of every lane as long as it
+// lives.
+__device__ __forceinline__ float uniform(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ ff uniform(ff v) { return {uniform(v.hi), uniform(v.lo)}; }
+
+constexpr int kIqAhead = 4;  // IQ modes: window entries of a pixel read ahead
+
 // a compile-time flag handed to the generic lambdas of the channel loop
 template <bool B> struct Flag { static constexpr bool value = B; };
 
@@ -324,9 +392,10 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   float *s_txq = (float *)smem;                        // [kMaxAngles] tx(q) - LT
   int *s_lt = (int *)(smem + kMaxAngles * 4);          // [kMaxAngles] LT
   float2 *s_tph = (float2 *)(smem + kMaxAngles * 8);   // [kMaxAngles] IQ: exp(2 pi i r (LT + off_t))
-  float4 *s_ch = (float4 *)(smem + kLdsAngleBytes);    // [chunk] {Dq, rq^2, rq, rx(q) - LR}
-  float2 *s_ph = (float2 *)(smem + plan_lds_ph_offset(P));  // [chunk] IQ: exp(2 pi i r (LR + off_r))
-  int2 *s_row = (int2 *)(smem + plan_lds_row_offset(P));  // [chunk * A] window rows
+  // channel table, P.tab channels from e_tab on
+  float4 *s_ch = (float4 *)(smem + kLdsAngleBytes);         // {Dq, rq^2, rq, rx(q) - LR - off_r}
+  float2 *s_ph = (float2 *)(smem + plan_lds_ph_offset(P));  // IQ: exp(2 pi i r (LR + off_r))
+  int *s_lr = (int *)(smem + plan_lds_lr_offset(P));        // LR
   float2 *s_pairs = (float2 *)(smem + plan_lds_win_offset(P));
   // DMAS, pDAS: per (wavefront, channel) {Dw, kR (int bits), rw, rx(w) - LR - off_r - kR}
   constexpr bool WREF = wave_ref_mode(MODE);
@@ -349,24 +418,22 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   const int iz = iz0 + wzi * lz + (pl & (lz - 1)), ix = ix0 + wxi * lx + (pl >> lzs);
   const int A = PRED ? P.n_angles : AM;
   const int N = P.n_channels, win = P.win, chunk = P.chunk;
-  // hk in a scalar register, hb in a vector one: the weight's FMA may read only
-  // one scalar operand, and an opaque hb is not re-derived in every iteration
-  const float hk = __int_as_float(
-      __builtin_amdgcn_readfirstlane(__float_as_int(P.apod == kHann ? 0.5f : 0.f)));
-  float hb = P.apod == kHann ? 0.5f : 1.f;
-  asm("" : "+v"(hb));
+  // hk and hb in vector registers, not re-derived in every iteration: an FMA
+  // with a scalar operand issues at half the rate of one without
+  float hk = P.apod == kHann ? 0.5f : 0.f, hb = P.apod == kHann ? 0.5f : 1.f;
+  asm("" : "+v"(hk), "+v"(hb));
 
   // Tile extent, clipped to the grid: lanes past the edge evaluate the edge
   // pixel again and write nothing, so every window only spans grid pixels.
   const int ixe = min(ix0 + TX - 1, P.nx - 1), ize = min(iz0 + TZ - 1, P.nz - 1);
   const int ixq = (ix0 + ixe) >> 1, izq = (iz0 + ize) >> 1;  // reference pixel q of the tile
   // the tile's offset range from q (window origins)
-  const float dxlo = (float)(ix0 - ixq) * P.DX, dxhi = (float)(ixe - ixq) * P.DX;
-  const float dzlo = (float)(iz0 - izq) * P.DZ, dzhi = (float)(ize - izq) * P.DZ;
+  const float dxlo = uniform((float)(ix0 - ixq) * P.DX), dxhi = uniform((float)(ixe - ixq) * P.DX);
+  const float dzlo = uniform((float)(iz0 - izq) * P.DZ), dzhi = uniform((float)(ize - izq) * P.DZ);
   // tile reference position in float-float
-  const ff Xq = ff_add(ff_mul({(float)ixq, 0.f}, {P.DX, P.DXl}), {P.X0, P.X0l});
-  const ff Zq = ff_add(ff_mul({(float)izq, 0.f}, {P.DZ, P.DZl}), {P.Z0, P.Z0l});
-  const float Zqf = ff_f(Zq);
+  const ff Xq = uniform(ff_add(ff_mul({(float)ixq, 0.f}, {P.DX, P.DXl}), {P.X0, P.X0l}));
+  const ff Zq = uniform(ff_add(ff_mul({(float)izq, 0.f}, {P.DZ, P.DZl}), {P.Z0, P.Z0l}));
+  const float Zqf = uniform(ff_f(Zq));
   // reference of the per-gather offsets: q, or the centre of the wavefront's
   // pixels (clipped to the tile's grid pixels) for DMAS and pDAS
   int ixr = ixq, izr = izq;
@@ -375,9 +442,11 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     ixr = (bx0 + min(bx0 + lx - 1, ixe)) >> 1;
     izr = (bz0 + min(bz0 + lz - 1, ize)) >> 1;
   }
-  const ff Xr = WREF ? ff_add(ff_mul({(float)ixr, 0.f}, {P.DX, P.DXl}), {P.X0, P.X0l}) : Xq;
-  const ff Zr = WREF ? ff_add(ff_mul({(float)izr, 0.f}, {P.DZ, P.DZl}), {P.Z0, P.Z0l}) : Zq;
-  const float Zrf = ff_f(Zr);
+  const ff Xr =
+      WREF ? uniform(ff_add(ff_mul({(float)ixr, 0.f}, {P.DX, P.DXl}), {P.X0, P.X0l})) : Xq;
+  const ff Zr =
+      WREF ? uniform(ff_add(ff_mul({(float)izr, 0.f}, {P.DZ, P.DZl}), {P.Z0, P.Z0l})) : Zq;
+  const float Zrf = uniform(ff_f(Zr));
   // the pixel's offsets from the reference
   const float dx = (float)(min(ix, ixe) - ixr) * P.DX;
   const float dz = (float)(min(iz, ize) - izr) * P.DZ;
@@ -397,6 +466,36 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   // of the loop over all channels.
   __shared__ int s_erange[2 * kMaxWavesPerBlock];
   const bool given_hull = hull_lo >= 0;
+
+  // The channel table: per channel the window origin LR and, except for DMAS
+  // and pDAS, the reference delay rx(q) in float-float and the terms of the
+  // receive-delay difference. It normally holds every channel (of a given hull:
+  // every one of the hull) and is filled once, beside the hull search and the
+  // angle constants and by other wavefronts than those; where the LDS does not
+  // hold it beside a window chunk, it is filled again every P.tab channels.
+  // Entries past the last channel (padding of several lane groups) repeat it.
+  auto fill_table = [&](int base, int n) __attribute__((always_inline)) {
+    const int bs = (int)blockDim.x, half = (bs >> 1) & -kWave;
+    for (int c = tid >= half ? tid - half : tid + bs - half; c < n; c += bs) {
+      const int e = min(base + c, N - 1);
+      const ff xe = {P.xe[e], P.xel[e]};
+      const ff dq = ff_add(Xq, ff_neg(xe));
+      const float dqf = ff_f(dq);
+      const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
+      s_lr[c] = (int)lr;
+      if constexpr (!WREF) {
+        const ff rq2 = ff_add(ff_mul(dq, dq), ff_mul(Zq, Zq));
+        const ff rq = ff_sqrt(rq2);
+        s_ch[c] = make_float4(dqf, ff_f(rq2), ff_f(rq) + 1e-20f,
+                              ff_f(ff_add(rq, {-(lr + (float)P.off_r), 0.f})));
+      }
+      if constexpr (IQ) s_ph[c] = carrier_phasor((int)lr + P.off_r, P.iq_r, P.iq_rl);
+    }
+  };
+  int e_tab = given_hull ? __builtin_amdgcn_readfirstlane(hull_lo) : 0;
+  const int tab_all = (given_hull ? __builtin_amdgcn_readfirstlane(hull_hi) : N) - e_tab + cpw - 1;
+  const bool tab_once = tab_all <= P.tab;
+  if (tab_once) fill_table(e_tab, tab_all);
   if (P.apod != kNone && !given_hull) {
     const float zmax = Zqf + dzhi;
     int lo = N, hi = 0;
@@ -493,46 +592,21 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     if (e0 > e_lo) __syncthreads();  // the previous chunk's windows have been read
     const int cnt = min(chunk, e_hi - e0);                   // channels of this chunk
     const int cnt_pad = ONEGRP ? cnt : (cnt + cpw - 1) / cpw * cpw;  // rows read
-    // Per-channel tile constants: the window origin LR, the reference delay
-    // rx(q) in float-float, and the terms of the receive-delay difference;
-    // channel c is taken by thread blockDim - 1 - c, so that these run in other
-    // wavefronts than the row table below, which starts at thread 0.
-    for (int c = (int)blockDim.x - 1 - tid; !WREF && c < cnt_pad; c += blockDim.x) {
-      const int e = min(e0 + c, N - 1);
-      const ff xe = {P.xe[e], P.xel[e]};
-      const ff dq = ff_add(Xq, ff_neg(xe));
-      const ff rq2 = ff_add(ff_mul(dq, dq), ff_mul(Zq, Zq));
-      const ff rq = ff_sqrt(rq2);
-      const float dqf = ff_f(dq);
-      const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
-      s_ch[c] = make_float4(dqf, ff_f(rq2), ff_f(rq) + 1e-20f,
-                            ff_f(ff_add(rq, {-(lr + (float)P.off_r), 0.f})));
-      if constexpr (IQ) s_ph[c] = carrier_phasor((int)lr + P.off_r, P.iq_r, P.iq_rl);
+    if (!tab_once && (e0 == e_lo || e0 + cnt_pad > e_tab + P.tab)) {
+      e_tab = e0;
+      fill_table(e0, min(P.tab, e_hi - e0 + cpw - 1));
+      __syncthreads();
     }
-    // Window rows r = c A + a: the record of (angle a, channel e0 + c) and the
-    // first sample LT_a + LR (LR from the same expression as above); rows of
-    // padding channels (past e_hi) read all zero. The record offset is a full
-    // 32-bit product (n_samples may exceed the 24-bit multiplier's range; the
-    // host bounds the product below 2^31).
-    const int rows = cnt_pad * A, off = P.off_t + P.off_r;
-    for (int r = tid; r < rows; r += blockDim.x) {
-      const int c = r / A, a = r - c * A;
-      const int e = min(e0 + c, N - 1);
-      const float dqf = ff_f(ff_add(Xq, ff_neg({P.xe[e], P.xel[e]})));
-      const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
-      s_row[r] = make_int2((__mul24(a, N) + e) * P.n_samples,
-                           e0 + c < e_hi ? s_lt[a] + (int)lr : -(1 << 30));
-    }
+    const int ct = e0 - e_tab;  // the chunk's first channel in the table
     if constexpr (WREF) {
       // every wavefront, for its own reference pixel and each channel of the
       // chunk: Dw = Xw - Xe, rw^2, rw, and rw - LR - off_r split into the
-      // integer kR and a fraction of at most 1/2 (LR from the same expression
-      // as the window rows)
+      // integer kR and a fraction of at most 1/2 (before the staging, whose
+      // barrier orders these writes before the gathers)
       for (int c = lane; c < cnt_pad; c += kWave) {
         const int e = min(e0 + c, N - 1);
         const ff xe = {P.xe[e], P.xel[e]};
-        const float dqf = ff_f(ff_add(Xq, ff_neg(xe)));
-        const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
+        const float lr = (float)s_lr[ct + c];
         const ff dw = ff_add(Xr, ff_neg(xe));
         const ff rw2 = ff_add(ff_mul(dw, dw), ff_mul(Zr, Zr));
         const ff rw = ff_sqrt(rw2);
@@ -543,15 +617,16 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
                                   (rrel.hi - k) + rrel.lo);
       }
     }
-    __syncthreads();
+    constexpr int AK = PRED ? 0 : AM;
+    const StageRows SR = {cnt_pad * A, A, e0, e_hi, P.off_t + P.off_r, s_lt, s_lr + ct};
     if constexpr (IQ)
-      stage_windows_iq(P, rows, off, s_row, (float4 *)s_pairs);
+      stage_windows_iq<AK>(P, SR, (float4 *)s_pairs);
     else if (P.dtype == kI16)
-      stage_windows<kI16, MODE>(P, rows, off, s_row, s_pairs);
+      stage_windows<kI16, MODE, AK>(P, SR, s_pairs);
     else if (P.dtype == kF16)
-      stage_windows<kF16, MODE>(P, rows, off, s_row, s_pairs);
+      stage_windows<kF16, MODE, AK>(P, SR, s_pairs);
     else
-      stage_windows<kF32, MODE>(P, rows, off, s_row, s_pairs);
+      stage_windows<kF32, MODE, AK>(P, SR, s_pairs);
     __syncthreads();
 
     const int wstride = win * P.entry_bytes;  // bytes between angle windows
@@ -563,7 +638,7 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     auto channel = [&](int k, auto sq) __attribute__((always_inline)) {
       const int c = ONEGRP ? k : k + grp;
       const int slot = wave * chunk + c;
-      const float4 ch = WREF ? s_chw[slot] : s_ch[c];
+      const float4 ch = WREF ? s_chw[slot] : s_ch[ct + c];
       // DMAS, pDAS: the wavefront's integer shift of this channel's window
       int kr = 0;
       if constexpr (WREF)
@@ -596,31 +671,48 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
       } else if constexpr (IQ) {
         // receive phasor of this (pixel, channel), weight folded in:
         // w exp(2 pi i r (LR + off_r + rx(p) - LR - off_r))
-        const float2 pk = s_ph[c];
+        const float2 pk = s_ph[ct + c];
         const float rho = P.iq_r * rxl;
         const float cr = __builtin_amdgcn_cosf(rho), sr = __builtin_amdgcn_sinf(rho);
         const float Rx = w * (pk.x * cr - pk.y * sr), Ry = w * (pk.x * sr + pk.y * cr);
+        // kIqAhead angles' entries are read before the first is used: left alone,
+        // the compiler reads one entry at a time (all eleven angles' entries
+        // would take 44 registers beside 33 of sums and transmit delays)
 #pragma unroll
-        for (int a = 0; a < AM; ++a) {
-          if (!PRED || a < A) {
-            const float s = txl[a] + rxl;
-            const int n = floor_i32(s);
-            const float4 q = *(const float4 *)(wb + a * wstride + (n << 4));
-            const float I = fmaf(s, q.y, q.x), Qv = fmaf(s, q.w, q.z);  // the lines at s
-            float cx = Rx, cy = Ry;
-            if constexpr (MODE == kBbdmas) {
-              // sqrt(amplitude), phase kept: scale by |q|^(-1/2). |q|^2 carries
-              // the smallest normal float, 2^-126, so that q = 0 gives a finite
-              // scale (at most 2^31.5) times a zero sample, with no test and
-              // select; above |q| = 2^-50 the added term lies below the float32
-              // rounding of |q|^2
-              const float m2 = fmaf(I, I, fmaf(Qv, Qv, 0x1p-126f));
-              const float k = __builtin_amdgcn_rsqf(__builtin_amdgcn_sqrtf(m2));
-              cx *= k;
-              cy *= k;
+        for (int g = 0; g < AM; g += kIqAhead) {
+          float sv[kIqAhead];
+          float4 qv[kIqAhead];
+#pragma unroll
+          for (int i = 0; i < kIqAhead; ++i) {
+            const int a = g + i;
+            if (a < AM && (!PRED || a < A)) {
+              sv[i] = txl[a < AM ? a : 0] + rxl;
+              qv[i] = *(const float4 *)(wb + a * wstride + (floor_i32(sv[i]) << 4));
             }
-            S[a] = fmaf(cx, I, fmaf(-cy, Qv, S[a]));
-            SI[a] = fmaf(cx, Qv, fmaf(cy, I, SI[a]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < kIqAhead; ++i) {
+            const int a = g + i;
+            if (a < AM && (!PRED || a < A)) {
+              const float4 q = qv[i];
+              const float I = fmaf(sv[i], q.y, q.x), Qv = fmaf(sv[i], q.w, q.z);  // lines at s
+              float cx = Rx, cy = Ry;
+              if constexpr (MODE == kBbdmas) {
+                // sqrt(amplitude), phase kept: scale by |q|^(-1/2). |q|^2 carries
+                // the smallest normal float, 2^-126, so that q = 0 gives a finite
+                // scale (at most 2^31.5) times a zero sample, with no test and
+                // select; above |q| = 2^-50 the added term lies below the float32
+                // rounding of |q|^2
+                const float m2 = fmaf(I, I, fmaf(Qv, Qv, 0x1p-126f));
+                const float k = __builtin_amdgcn_rsqf(__builtin_amdgcn_sqrtf(m2));
+                cx *= k;
+                cy *= k;
+              }
+              const int t = a < AM ? a : 0;
+              S[t] = fmaf(cx, I, fmaf(-cy, Qv, S[t]));
+              SI[t] = fmaf(cx, Qv, fmaf(cy, I, SI[t]));
+            }
           }
         }
       } else if constexpr (MODE == kPdas) {

@@ -17,8 +17,16 @@ namespace pwbf {
 
 namespace {
 
+// Wavefronts per SIMD the register allocation leaves room for: three 8-wavefront
+// blocks per CU, as many as the default LDS budget holds, up to 16 angles (IQ:
+// 11, two sums and a transmit delay each), two beyond. 11-angle 1024 x 1024
+// frames: IQ-DAS 222 -> 185 us and BB-DMAS 311 -> 277 us at 80 registers (six
+// wavefronts, the entries read kIqAhead at a time) instead of 108 (four).
+constexpr int min_waves(int am, int mode) { return am <= (is_iq_mode(mode) ? 11 : 16) ? 6 : 4; }
+
 template <int AM, bool PRED, int MODE, bool ONEGRP>
-__global__ void __launch_bounds__(kWave * kMaxWavesPerBlock) k_beamform(const FramePlan P) {
+__global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
+    __attribute__((amdgpu_waves_per_eu(min_waves(AM, MODE)))) k_beamform(const FramePlan P) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
   // RF modes: clear the frame maximum the post-processing folds into (the IQ

@@ -275,23 +275,37 @@ static int fit_tile(const pwbf_geometry *g, pwbf_tile t, FramePlan *P, std::stri
                 "beamformer, which keeps float32 delay offsets under %d samples); use a "
                 "shallower or narrower tile",
                 TZ, TX, P->win, wmax, wmax / 2);
+  // What is accepted: the windows of the chunk with 8 bytes per window row and
+  // 16 (IQ: 24) per channel beside them fit a block's LDS. A chunk chosen here
+  // holds as many channels as the default budget (each tile walks only its own
+  // active aperture, so the chunks start wherever that begins).
   const size_t per_channel = (size_t)P->n_angles * (P->win * P->entry_bytes + 8) +
                              (is_iq_mode(P->mode) ? 24 : 16) +
                              (wave_ref_mode(P->mode) ? (size_t)t.wz * t.wx * 16 : 0);
   const size_t fixed = kLdsAngleBytes + 16;
+  const int nch = (g->n_channels + t.cpw - 1) / t.cpw * t.cpw;
   int chunk = t.chunk;
   if (chunk == 0) {
-    // as many channels as the default budget holds (each tile walks only its
-    // own active aperture, so the chunks start wherever that begins)
     const int fit = (int)((kDefaultLdsBytes - fixed) / per_channel) / t.cpw * t.cpw;
-    const int nch = (g->n_channels + t.cpw - 1) / t.cpw * t.cpw;
     chunk = std::max(t.cpw, std::min(fit, nch));
   }
   P->chunk = chunk;
-  if (P->chunk < t.cpw || plan_lds_bytes(*P) > (size_t)kMaxLdsBytes)
+  const size_t need = fixed - 16 + (size_t)chunk * per_channel;
+  if (P->chunk < t.cpw || (need + 15) / 16 * 16 > (size_t)kMaxLdsBytes)
     return fail(err, PWBF_E_UNSUPPORTED,
-                "tile needs %zu bytes of LDS per block (limit %d); use a smaller tile",
-                plan_lds_bytes(*P), kMaxLdsBytes);
+                "tile needs %zu bytes of LDS per block (limit %d); use a smaller tile", need,
+                kMaxLdsBytes);
+  // The channel table holds every channel where it fits beside the chunk (a
+  // smaller chunk chosen here makes room), else as many channels as the chunk,
+  // which needs no more than the row table counted above.
+  P->tab = g->n_channels + t.cpw - 1;
+  if (t.chunk == 0)
+    while (P->chunk > t.cpw && plan_lds_bytes(*P) > (size_t)kDefaultLdsBytes) P->chunk -= t.cpw;
+  if (plan_lds_bytes(*P) > (size_t)kMaxLdsBytes ||
+      (t.chunk == 0 && plan_lds_bytes(*P) > (size_t)kDefaultLdsBytes)) {
+    P->chunk = chunk;
+    P->tab = chunk;
+  }
   return PWBF_OK;
 }
 

@@ -73,7 +73,8 @@ struct FramePlan {
   int32_t win;           // LDS entries per (channel, angle) window
   int32_t off_t, off_r;  // centring offsets of the transmit and receive window delays
   int32_t tile_z, tile_x;  // pixels per tile: lz * wz by lx * wx
-  int32_t tiles_z, tiles_x, n_tiles, reserved_i32;
+  int32_t tiles_z, tiles_x, n_tiles;
+  int32_t tab;  // channels the LDS channel table holds
   float sa[kMaxAngles], sal[kMaxAngles];  // sin(theta_a), hi and lo
   float ca[kMaxAngles], cal[kMaxAngles];  // cos(theta_a)
   float to[kMaxAngles], tol[kMaxAngles];  // first-firing offset plus t0, samples
@@ -98,27 +99,29 @@ struct PostPlan {
 // near zero crossings); DAS and the IQ modes keep the tile reference.
 PWBF_HD constexpr bool wave_ref_mode(int mode) { return mode == kDmas || mode == kPdas; }
 
-// LDS of a block: per angle {tx(q) - LT, LT, transmit phasor} (16 bytes), per
-// channel of the chunk {Dq, rq^2, rq, rx(q) - LR} (16) and the receive phasor
-// (8, IQ modes only), per (wavefront, channel) of the chunk the wavefront's
-// reference terms and integer window offset (16, DMAS and pDAS only), per
-// window row (channel, angle) of the chunk its record offset and first sample
-// (8), then the windows.
+// LDS of a block: per angle {tx(q) - LT, LT, transmit phasor} (16 bytes); the
+// channel table, per channel {Dq, rq^2, rq, rx(q) - LR} (16, not DMAS and pDAS),
+// the receive phasor (8, IQ modes only) and the window origin LR (4); per
+// (wavefront, channel) of the chunk the wavefront's reference terms and integer
+// window offset (16, DMAS and pDAS only); then the windows of the chunk.
 constexpr size_t kLdsAngleBytes = kMaxAngles * 16;
+PWBF_HD constexpr size_t lds_table_bytes(int mode) {  // per channel of the table
+  return (wave_ref_mode(mode) ? 0 : 16) + (is_iq_mode(mode) ? 8 : 0) + 4;
+}
 PWBF_HD inline size_t plan_lds_ph_offset(const FramePlan &p) {
-  return kLdsAngleBytes + (size_t)p.chunk * 16;
+  return kLdsAngleBytes + (wave_ref_mode(p.mode) ? 0 : (size_t)p.tab * 16);
+}
+PWBF_HD inline size_t plan_lds_lr_offset(const FramePlan &p) {
+  return plan_lds_ph_offset(p) + (is_iq_mode(p.mode) ? (size_t)p.tab * 8 : 0);
 }
 PWBF_HD inline size_t plan_lds_wref_offset(const FramePlan &p) {
-  return plan_lds_ph_offset(p) + (is_iq_mode(p.mode) ? (size_t)p.chunk * 8 : 0);
+  return (plan_lds_lr_offset(p) + (size_t)p.tab * 4 + 15) / 16 * 16;
 }
 PWBF_HD inline size_t plan_lds_wref_bytes(const FramePlan &p) {
   return wave_ref_mode(p.mode) ? (size_t)p.wz * p.wx * p.chunk * 16 : 0;
 }
-PWBF_HD inline size_t plan_lds_row_offset(const FramePlan &p) {
-  return plan_lds_wref_offset(p) + plan_lds_wref_bytes(p);
-}
 PWBF_HD inline size_t plan_lds_win_offset(const FramePlan &p) {
-  return (plan_lds_row_offset(p) + (size_t)p.chunk * p.n_angles * 8 + 15) / 16 * 16;
+  return plan_lds_wref_offset(p) + plan_lds_wref_bytes(p);
 }
 PWBF_HD inline size_t plan_lds_bytes(const FramePlan &p) {
   return plan_lds_win_offset(p) + (size_t)p.chunk * p.n_angles * p.win * p.entry_bytes;
