@@ -11,6 +11,7 @@
 
 #include "../../include/pwbf.h"
 #include "batch.h"
+#include "post_layout.h"
 #include "plan_host.h"
 
 namespace pwbf {
@@ -48,8 +49,8 @@ struct pwbf_batch {
   hipStream_t cap = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  int n_items = 0, n_post_cols = 0, n_log_cols = 0, blocks = 0, blocks_per_cu = 0;
-  int lds = 0, max_nz = 0, graph_nodes = 0;
+  int n_items = 0, n_columns = 0, n_post_cols = 0, n_log_cols = 0, blocks = 0, blocks_per_cu = 0;
+  int lds = 0, graph_nodes = 0;
 };
 
 namespace {
@@ -324,7 +325,6 @@ int pwbf_batch_create(const pwbf_frame *frames, int32_t n, int32_t flags, void *
       frame_work[i].push_back({c, i, t});
       frame_cost[i] += c;
     }
-    if (pwbf::post_needed(&f.out)) b->max_nz = std::max(b->max_nz, f.geom->nz);
   }
   // Frames go to up to kMaxBranches graph branches, longest first, each to the
   // branch with the least work so far; branches run side by side, so each
@@ -378,7 +378,10 @@ int pwbf_batch_create(const pwbf_frame *frames, int32_t n, int32_t flags, void *
     for (int i = 0; i < n; ++i) {
       const pwbf_frame &f = frames[i];
       if (branch_of[i] != k || !pwbf::post_needed(&f.out)) continue;
-      for (int ix = 0; ix < f.geom->nx; ++ix) post_cols.push_back(make_int2(i, ix));
+      // one block per run of columns (post_layout.h)
+      const int run = pwbf::post_columns(b->post[i].log2nz, pwbf::kPostThreads);
+      for (int ix = 0; ix < f.geom->nx; ix += run) post_cols.push_back(make_int2(i, ix));
+      b->n_columns += f.geom->nx;
       if (f.out.logimg)
         for (int ix = 0; ix < f.geom->nx; ++ix) log_cols.push_back(make_int2(i, ix));
     }
@@ -457,7 +460,7 @@ int pwbf_batch_create(const pwbf_frame *frames, int32_t n, int32_t flags, void *
                                             b->classes.data() + br.class_first, br.class_n,
                                             b->d_post_cols + br.post_first, br.post_n,
                                             b->d_log_cols + br.log_first, br.log_n, b->lds,
-                                            b->max_nz, step, b->fork_streams[k]);
+                                            step, b->fork_streams[k]);
       }
     for (int k = 0; k < n_br && le == hipSuccess; ++k) {
       le = hipEventRecord(b->fork_events[k], b->fork_streams[k]);
@@ -540,7 +543,7 @@ int pwbf_batch_describe(const pwbf_batch *b, pwbf_batch_info *info) {
   if (!b || !info) return api_set_error(PWBF_E_INVALID, "batch or info is NULL");
   info->n_frames = b->n;
   info->n_items = b->n_items;
-  info->n_columns = b->n_post_cols;
+  info->n_columns = b->n_columns;
   info->blocks = b->blocks;
   info->blocks_per_cu = b->blocks_per_cu;
   info->lds_bytes = b->lds;

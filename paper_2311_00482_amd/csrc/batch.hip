@@ -8,7 +8,7 @@
 //                      of its list, the items sorted by estimated tile cost
 //                      (active aperture x pixels x angles), largest first, so the
 //                      hardware dispatcher starts the longest tiles first
-//   k_batch_postz      one block per (frame, depth column) of its frames
+//   k_batch_postz      one block per (frame, run of depth columns) of its frames
 //   k_batch_logc       one block per (frame, depth column) with a log image
 // and the branches run side by side on the device, so one branch's
 // post-processing and tail overlap the others' beamforming. k_batch_reset
@@ -78,11 +78,11 @@ hipError_t class_occupancy(size_t lds, int *blocks_per_cu) {
   X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) \
   X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
 
-__global__ void __launch_bounds__(dev::kPostThreads)
+__global__ void __launch_bounds__(kPostThreads) __attribute__((amdgpu_waves_per_eu(4)))
     k_batch_postz(const PostPlan *__restrict__ post, const int2 *__restrict__ cols) {
   extern __shared__ __align__(16) float2 sm[];
-  const int2 c = cols[blockIdx.x];
-  dev::postz_column(post[c.x], c.y, sm);
+  const int2 c = cols[blockIdx.x];  // frame, first column
+  dev::postz_columns_any(post[__builtin_amdgcn_readfirstlane(c.x)], c.y, sm);
 }
 
 __global__ void __launch_bounds__(256)
@@ -124,7 +124,7 @@ int batch_branch_steps(int n_classes, int n_post_cols, int n_log_cols) {
 hipError_t launch_batch_branch_step(const FramePlan *plans, const PostPlan *post,
                                     const int4 *items, const BatchClass *classes, int n_classes,
                                     const int2 *post_cols, int n_post_cols, const int2 *log_cols,
-                                    int n_log_cols, size_t lds, int max_nz, int step,
+                                    int n_log_cols, size_t lds, int step,
                                     hipStream_t stream) {
   if (step < n_classes) {
     const BatchClass &k = classes[step];
@@ -139,9 +139,8 @@ hipError_t launch_batch_branch_step(const FramePlan *plans, const PostPlan *post
   }
   step -= n_classes;
   if (n_post_cols > 0 && step-- == 0) {
-    const size_t plds = dev::post_lds_bytes(max_nz);
-    hipLaunchKernelGGL(k_batch_postz, dim3(n_post_cols), dim3(dev::kPostThreads), plds, stream,
-                       post, post_cols);
+    hipLaunchKernelGGL(k_batch_postz, dim3(n_post_cols), dim3(kPostThreads),
+                       dev::kPostBatchLdsBytes, stream, post, post_cols);
     return hipGetLastError();
   }
   if (n_log_cols > 0 && step == 0) {

@@ -50,7 +50,9 @@ namespace pwbf {
 namespace {
 
 using dev::ff;
-using dev::kPostThreads;
+using fft::cmul;
+
+constexpr int kFkThreads = fft::kThreads;  // every block runs the in-LDS transforms
 
 template <int DT>
 __device__ __forceinline__ float trace_sample(const void *rf, size_t i) {
@@ -86,7 +88,7 @@ __device__ __forceinline__ int kbins_of(const FkPlan &F) { return (1 << F.log2nt
 // is zero). With Z its DFT and Z(Nt) = Z(0), the traces' spectra are
 // X0(k) = (Z(k) + conj Z(Nt - k)) / 2 and X1(k) = (Z(k) - conj Z(Nt - k)) / (2i).
 template <int DT>
-__global__ void __launch_bounds__(kPostThreads) k_fk_time(FkPlan F) {
+__global__ void __launch_bounds__(kFkThreads) k_fk_time(FkPlan F) {
   extern __shared__ __align__(16) float2 sm[];
   const int nt = 1 << F.log2nt, kbins = kbins_of(F), e0 = 2 * blockIdx.x, a = blockIdx.y;
   const bool two = e0 + 1 < F.n_ch;
@@ -95,7 +97,7 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_time(FkPlan F) {
   float2 *x = sm;
   const size_t base = ((size_t)a * F.n_ch + e0) * nt;
   const size_t base1 = two ? base + nt : base;  // every read inside the record array
-  for (int k = threadIdx.x; k < nt; k += kPostThreads) {
+  for (int k = threadIdx.x; k < nt; k += kFkThreads) {
     const float v1 = trace_sample<DT>(F.rf, base1 + k);
     x[fft::pad(k)] = make_float2(trace_sample<DT>(F.rf, base + k), two ? v1 : 0.f);
   }
@@ -107,31 +109,31 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_time(FkPlan F) {
   // T[a][k / R][e][k mod R]: the pair's rows of a block are adjacent, 2 R bins
   const int LR = 12 - F.log2nx, R = 1 << LR;
   float2 *T0 = F.T + (size_t)a * F.n_ch * fk_kbins_padded(F.log2nt, F.log2nx) + e0 * R;
-  // exp(2 pi i k c) at the thread's first bin, then by the step of kPostThreads
+  // exp(2 pi i k c) at the thread's first bin, then by the step of kFkThreads
   // bins: a thread's bins are at most 9 products from an accurate phase
   float sn, cs;
   sincospif(2.0f * frac_revs(threadIdx.x, c0), &sn, &cs);
   float2 ph0 = make_float2(cs, sn);
-  sincospif(2.0f * frac_revs(kPostThreads, c0), &sn, &cs);
+  sincospif(2.0f * frac_revs(kFkThreads, c0), &sn, &cs);
   const float2 step0 = make_float2(cs, sn);
   sincospif(2.0f * frac_revs(threadIdx.x, c1), &sn, &cs);
   float2 ph1 = make_float2(cs, sn);
-  sincospif(2.0f * frac_revs(kPostThreads, c1), &sn, &cs);
+  sincospif(2.0f * frac_revs(kFkThreads, c1), &sn, &cs);
   const float2 step1 = make_float2(cs, sn);
-  for (int k = threadIdx.x; k < kbins; k += kPostThreads) {
+  for (int k = threadIdx.x; k < kbins; k += kFkThreads) {
     const float2 z = x[fft::pad(k)], w = x[fft::pad((nt - k) & (nt - 1))];  // Z(k), Z(Nt - k)
     const float2 x0 = make_float2(0.5f * (z.x + w.x), 0.5f * (z.y - w.y));
     const float2 x1 = make_float2(0.5f * (z.y + w.y), 0.5f * (w.x - z.x));
     float2 *t = T0 + (size_t)(k >> LR) * F.n_ch * R + (k & (R - 1));
-    t[0] = dev::cmul(x0, ph0);
-    if (two) t[R] = dev::cmul(x1, ph1);
-    ph0 = dev::cmul(ph0, step0);
-    ph1 = dev::cmul(ph1, step1);
+    t[0] = cmul(x0, ph0);
+    if (two) t[R] = cmul(x1, ph1);
+    ph0 = cmul(ph0, step0);
+    ph1 = cmul(ph1, step1);
   }
 }
 
 template <int L, int METHOD>
-__global__ void __launch_bounds__(kPostThreads) k_fk_space(FkPlan F) {
+__global__ void __launch_bounds__(kFkThreads) k_fk_space(FkPlan F) {
   constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L, stride = fft::row_stride(nx, ROWS);
   extern __shared__ __align__(16) float2 sm[];
   float2 *x = sm;
@@ -139,7 +141,7 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_space(FkPlan F) {
   // the block's bins of every channel are one contiguous run of T (bins past
   // the last are never written and read as zero)
   const float2 *T = F.T + ((size_t)a * fk_kbins_padded(F.log2nt, L) + k0) * F.n_ch;
-  for (int t = threadIdx.x; t < nx * ROWS; t += kPostThreads) {
+  for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
     const int e = t / ROWS, r = t - e * ROWS, k = k0 + r;
     x[r * stride + fft::pad(e)] = (e < F.n_ch && k < kbins) ? T[t] : make_float2(0.f, 0.f);
   }
@@ -149,12 +151,12 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_space(FkPlan F) {
   if (METHOD == kFkStolt) {
     // Stolt's remap reads along frequency at fixed kx: store P[m][k], consecutive
     // threads on consecutive bins
-    for (int t = threadIdx.x; t < nx * ROWS; t += kPostThreads) {
+    for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
       const int m = t / ROWS, r = t - m * ROWS, k = k0 + r;
       if (k < kbins) P[(size_t)m * kbins + k] = x[r * stride + fft::pad(m)];
     }
   } else {
-    for (int t = threadIdx.x; t < nx * ROWS; t += kPostThreads) {
+    for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
       const int r = t >> L, m = t & (nx - 1), k = k0 + r;
       if (k < kbins) P[(size_t)k * nx + m] = x[r * stride + fft::pad(m)];
     }
@@ -203,12 +205,12 @@ __device__ __forceinline__ ff ff_sub_mul(ff v, ff u, float c_hi, float c_lo) {
 template <int L>
 struct RemapCells {
   static constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L;
-  static constexpr int MPT = nx >= kPostThreads ? nx / kPostThreads : 1;  // columns per thread
-  static constexpr int RSTEP = nx >= kPostThreads ? 1 : kPostThreads / nx;  // rows apart
+  static constexpr int MPT = nx >= kFkThreads ? nx / kFkThreads : 1;  // columns per thread
+  static constexpr int RSTEP = nx >= kFkThreads ? 1 : kFkThreads / nx;  // rows apart
   __device__ static int m(int mi) {
-    return nx >= kPostThreads ? (int)threadIdx.x + kPostThreads * mi : (int)threadIdx.x & (nx - 1);
+    return nx >= kFkThreads ? (int)threadIdx.x + kFkThreads * mi : (int)threadIdx.x & (nx - 1);
   }
-  __device__ static int r0() { return nx >= kPostThreads ? 0 : (int)threadIdx.x >> L; }
+  __device__ static int r0() { return nx >= kFkThreads ? 0 : (int)threadIdx.x >> L; }
 };
 
 // Stolt's remap of the block's rows: the cell (j, m) takes the data spectrum at
@@ -222,7 +224,7 @@ __device__ __forceinline__ void stolt_rows(const FkAngleConst &A, const float2 *
   constexpr int stride = fft::row_stride(nx, ROWS);
   static_assert((1 << LR) == ROWS, "rows of a block");
 #pragma unroll 4
-  for (int t = threadIdx.x; t < kFkRowPoints; t += kPostThreads) {
+  for (int t = threadIdx.x; t < kFkRowPoints; t += kFkThreads) {
     const int r = t & (ROWS - 1), m = t >> LR, ms = m < nx / 2 ? m : m - nx;
     const int j = min(j0 + r, kbins - 1);  // rows past the last bin store zero below
     const float fj = (float)j;
@@ -299,7 +301,7 @@ __device__ __forceinline__ void lu_rows(const FkAngleConst &A, const float2 *__r
 }
 
 template <int L, int METHOD>
-__global__ void __launch_bounds__(kPostThreads) k_fk_remap(FkPlan F) {
+__global__ void __launch_bounds__(kFkThreads) k_fk_remap(FkPlan F) {
   constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L, stride = fft::row_stride(nx, ROWS);
   extern __shared__ __align__(16) float2 sm[];
   float2 *x = sm;
@@ -314,13 +316,13 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_remap(FkPlan F) {
   fft::transform<L, true, ROWS>(x);
   // the window's columns, transposed: consecutive threads take consecutive rows
   float2 *U = F.U + (size_t)a * nx * kbins;
-  for (int t = threadIdx.x; t < A.ncol * ROWS; t += kPostThreads) {
+  for (int t = threadIdx.x; t < A.ncol * ROWS; t += kFkThreads) {
     const int c = t / ROWS, r = t - c * ROWS, j = j0 + r, e = A.col0 + c;
     if (j < kbins) U[(size_t)e * kbins + j] = x[r * stride + fft::pad(e)];
   }
 }
 
-__global__ void __launch_bounds__(kPostThreads) k_fk_itime(FkPlan F) {
+__global__ void __launch_bounds__(kFkThreads) k_fk_itime(FkPlan F) {
   extern __shared__ __align__(16) float2 sm[];
   const int a = blockIdx.y;
   const FkAngleConst &A = F.ang[a];
@@ -329,13 +331,13 @@ __global__ void __launch_bounds__(kPostThreads) k_fk_itime(FkPlan F) {
   const int col = A.col0 + blockIdx.x;
   float2 *x = sm;
   const float2 *I = F.U + ((size_t)a * nx + col) * kbins;
-  for (int j = threadIdx.x; j < nt; j += kPostThreads)
+  for (int j = threadIdx.x; j < nt; j += kFkThreads)
     x[fft::pad(j)] = j < kbins ? I[j] : make_float2(0.f, 0.f);
   __syncthreads();
   fft::transform_any<true>(x, F.log2nt);
   const float scale = 1.0f / ((float)nx * (float)nt);
   float2 *out = F.M + ((size_t)a * nx + col) * nt;
-  for (int l = A.row0 + threadIdx.x; l < A.row0 + A.nrow; l += kPostThreads) {
+  for (int l = A.row0 + threadIdx.x; l < A.row0 + A.nrow; l += kFkThreads) {
     const float2 v = x[fft::pad(l)];
     out[l] = make_float2(v.x * scale, v.y * scale);
   }
@@ -462,7 +464,7 @@ template <int L>
 hipError_t launch_rows(const FkPlan &F, hipStream_t s) {
   constexpr int ROWS = kFkRowPoints >> L;
   const int kbins = (1 << F.log2nt) / 2 + 1;
-  const dim3 grid((kbins + ROWS - 1) / ROWS, F.n_ang), blk(kPostThreads);
+  const dim3 grid((kbins + ROWS - 1) / ROWS, F.n_ang), blk(kFkThreads);
   const size_t lds = fft::lds_bytes(1 << L, ROWS);
   if (F.method == kFkLu) {
     hipLaunchKernelGGL((k_fk_space<L, kFkLu>), grid, blk, lds, s, F);
@@ -483,7 +485,7 @@ hipError_t launch_rows(const FkPlan &F, hipStream_t s) {
 hipError_t launch_fk(const FkPlan &F, int ncol_max, hipStream_t s) {
   const int nt = 1 << F.log2nt;
   const size_t lds_t = fft::lds_bytes(nt, 1);
-  const dim3 blk(kPostThreads);
+  const dim3 blk(kFkThreads);
   hipError_t e;
   const dim3 pairs((F.n_ch + 1) / 2, F.n_ang);  // two traces per block
   if (F.dtype == kI16)

@@ -1,5 +1,5 @@
-// Baseband (IQ) demodulation of channel records, two records per block, and
-// the decimating form, one record per block.
+// Baseband (IQ) demodulation of channel records, two records per transform, and
+// the decimating form, one record per transform (fft_reg.h).
 //
 // The analytic signal of a record x of n = 2^L samples is the inverse DFT of
 // its spectrum times the one-sided weights w(k) (1 at DC and Nyquist, 2 on
@@ -7,8 +7,8 @@
 // is x itself and its imaginary part is the discrete Hilbert transform H(x).
 // Two records x1, x2 go through one transform pair: the inverse DFT of w(k)
 // times the DFT of x1 + i x2 is (x1 + i H(x1)) + i (x2 + i H(x2)), so
-// H(x1) = Im - x2 and H(x2) = x1 - Re, with x1 and x2 the samples kept in
-// registers. Each analytic record is then multiplied by exp(-2 pi i r k) with
+// H(x1) = Im - x2 and H(x2) = x1 - Re, with x1 and x2 the samples read
+// again. Each analytic record is then multiplied by exp(-2 pi i r k) with
 // r = f0 / fs, k the sample index. The carrier phase is formed in revolutions
 // from r as a float-float pair: k * r_hi splits exactly into a rounded product
 // and its error (one FMA), so frac(k r) is accurate to ~1e-7 revolutions for
@@ -22,7 +22,7 @@ namespace pwbf {
 
 namespace {
 
-using dev::kPostThreads;
+using fft::cmul;
 
 template <int DT>
 __device__ __forceinline__ float rf_sample(const void *rf, size_t i) {
@@ -30,8 +30,6 @@ __device__ __forceinline__ float rf_sample(const void *rf, size_t i) {
   if constexpr (DT == kF16) return __half2float(((const __half *)rf)[i]);
   return ((const float *)rf)[i];
 }
-
-constexpr int kIqMaxPerThread = 4096 / kPostThreads;  // samples of a record per thread
 
 // exp(-2 pi i r k): the carrier phase at sample k in revolutions, from r as a
 // float-float pair (the FMA gives the exact error of the rounded product); the
@@ -45,112 +43,161 @@ __device__ __forceinline__ float2 carrier(int k, float r_hi, float r_lo) {
   return make_float2(__builtin_amdgcn_cosf(rho), -__builtin_amdgcn_sinf(rho));
 }
 
-template <int DT>
-__global__ void __launch_bounds__(kPostThreads)
-    k_iq_demod(const void *__restrict__ rf, float2 *__restrict__ iq, int rows, int log2ns,
-               float r_hi, float r_lo) {
+// What bounds it at 4096 samples is the two transforms' VALU work and LDS
+// exchanges (69 MB read and written would take 13 us): 1408 records in 20.0 us,
+// 22.1 us with the transforms in LDS.
+template <int DT, int L>
+__global__ void __launch_bounds__(post_block(L)) __attribute__((amdgpu_waves_per_eu(4)))
+    k_iq_demod(const void *__restrict__ rf, float2 *__restrict__ iq, int rows, float r_hi,
+               float r_lo) {
+  using namespace fftr;
   extern __shared__ __align__(16) float2 sm[];
-  const int ns = 1 << log2ns;
-  float2 *x = sm;
-  const int r0 = 2 * blockIdx.x;
-  const bool two = r0 + 1 < rows;  // a missing second record is zero
-  const size_t base0 = (size_t)r0 * ns, base1 = two ? base0 + ns : base0;
-  float2 keep[kIqMaxPerThread];  // (x1, x2) at the thread's samples
+  constexpr int n = 1 << L, T = threads(L), E = points(L);
+  const int row = (int)threadIdx.x / T, t = (int)threadIdx.x & (T - 1);
+  // records past the last one are read again from it and not written; a missing
+  // second record is zero
+  const int r0 = 2 * ((int)blockIdx.x * post_columns(L, post_block(L)) + row);
+  const bool one = r0 < rows, two = r0 + 1 < rows;
+  const size_t base0 = (size_t)min(r0, rows - 1) * n, base1 = two ? base0 + n : base0;
+  auto samples = [&](const void *p, int e) __attribute__((always_inline)) {  // (x1, x2)
+    const int k = index_of<L, false>(e, t);
+    const float v1 = rf_sample<DT>(p, base1 + k);
+    return make_float2(rf_sample<DT>(p, base0 + k), two ? v1 : 0.f);
+  };
+  float2 v[E];
 #pragma unroll
-  for (int i = 0; i < kIqMaxPerThread; ++i) {
-    const int k = threadIdx.x + i * kPostThreads;
-    if (k < ns) {
-      const float v1 = rf_sample<DT>(rf, base1 + k);
-      keep[i] = make_float2(rf_sample<DT>(rf, base0 + k), two ? v1 : 0.f);
-      x[fft::pad(k)] = keep[i];
-    }
-  }
-  __syncthreads();
-  fft::transform_any<false>(x, log2ns);
-  const float inv_n = 1.0f / (float)ns;
-  for (int k = threadIdx.x; k < ns; k += kPostThreads) {
-    const float h = dev::analytic_weight(k, ns) * inv_n;
-    const float2 v = x[fft::pad(k)];
-    x[fft::pad(k)] = make_float2(v.x * h, v.y * h);
-  }
-  __syncthreads();
-  fft::transform_any<true>(x, log2ns);
+  for (int e = 0; e < E; ++e) v[e] = samples(rf, e);
+  filter<L>(v, sm + row * padded<L>(), t, [](int k) __attribute__((always_inline)) {
+    return dev::analytic_weight(k, n) * (1.0f / n);
+  });
+  // the samples again, from the cache (kept in registers, they spill at four
+  // wavefronts per SIMD): an address the compiler cannot tell is the same
+  const void *again = rf;
+  asm("" : "+s"(again));
 #pragma unroll
-  for (int i = 0; i < kIqMaxPerThread; ++i) {
-    const int k = threadIdx.x + i * kPostThreads;
-    if (k < ns) {
-      const float2 w = x[fft::pad(k)];
-      const float2 ph = carrier(k, r_hi, r_lo);
-      iq[base0 + k] = dev::cmul(make_float2(keep[i].x, w.y - keep[i].y), ph);
-      if (two) iq[base1 + k] = dev::cmul(make_float2(keep[i].y, keep[i].x - w.x), ph);
-    }
+  for (int e = 0; e < E; ++e) {
+    const int k = index_of<L, false>(e, t);
+    const float2 ph = carrier(k, r_hi, r_lo);
+    const float2 x12 = samples(again, e);
+    if (one) iq[base0 + k] = cmul(make_float2(x12.x, v[e].y - x12.y), ph);
+    if (two) iq[base1 + k] = cmul(make_float2(x12.y, x12.x - v[e].x), ph);
   }
 }
 
-// Decimation by D = 2^log2d, one record per block: the analytic signal is
-// band-limited to the bins k_lo..k_hi (those within fs / (2 D) of f0, decided
-// on the host) before the inverse transform, then mixed down, and every D-th
-// sample is kept. The band limit takes the real part off the record itself, so
-// the two-records-per-transform form above does not apply here.
-template <int DT>
-__global__ void __launch_bounds__(kPostThreads)
-    k_iq_demod_decim(const void *__restrict__ rf, float2 *__restrict__ iq, int log2ns,
-                     int log2d, int k_lo, int k_hi, float r_hi, float r_lo) {
+// Decimation by D = 2^LD, one record per transform: of the analytic spectrum only
+// the bins k_lo..k_hi are kept (those within fs / (2 D) of f0, decided on the
+// host), then mixed down, and every D-th sample is kept. The band limit takes the
+// real part off the record itself, so the two-records-per-transform form above
+// does not apply here. The kept bins are fewer than n / D apart, so they fall on
+// different bins of the n / D-point spectrum of the kept samples (bin k mod n / D):
+// the inverse transform has n / D points (448 records of 2048 samples at D = 2:
+// 10.5 -> 8.5 us). Its row needs only a part of the threads
+// of the record's (T / T2 copies of them compute the same, each on LDS of its own).
+template <int DT, int L, int LD>
+__global__ void __launch_bounds__(post_block(L))
+    k_iq_demod_decim(const void *__restrict__ rf, float2 *__restrict__ iq, int rows, int k_lo,
+                     int k_hi, float r_hi, float r_lo) {
+  using namespace fftr;
   extern __shared__ __align__(16) float2 sm[];
-  const int ns = 1 << log2ns;
-  float2 *x = sm;
-  const size_t base = (size_t)blockIdx.x * ns;
-  for (int k = threadIdx.x; k < ns; k += kPostThreads)
-    x[fft::pad(k)] = make_float2(rf_sample<DT>(rf, base + k), 0.f);
-  __syncthreads();
-  fft::transform_any<false>(x, log2ns);
-  const float inv_n = 1.0f / (float)ns;
-  for (int k = threadIdx.x; k < ns; k += kPostThreads) {
-    const float h = (k >= k_lo && k <= k_hi) ? dev::analytic_weight(k, ns) * inv_n : 0.f;
-    const float2 v = x[fft::pad(k)];
-    x[fft::pad(k)] = make_float2(v.x * h, v.y * h);
+  constexpr int n = 1 << L, T = threads(L), E = points(L);
+  constexpr int L2 = L - LD, n2 = 1 << L2, T2 = threads(L2), E2 = points(L2);
+  static_assert((T / T2) * padded<L2>() <= padded<L>(), "the copies fit the record's LDS");
+  const int row = (int)threadIdx.x / T, t = (int)threadIdx.x & (T - 1);
+  float2 *x = sm + row * padded<L>();
+  const int rec = (int)blockIdx.x * post_columns(L, post_block(L)) + row;
+  const size_t base = (size_t)min(rec, rows - 1) * n;
+  float2 v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    v[e] = make_float2(rf_sample<DT>(rf, base + index_of<L, false>(e, t)), 0.f);
+  TwiddlesOf<L, false> fwd;
+  fwd.load(t);
+  transform<L, false>(v, fwd, x, t);
+  TwiddlesOf<L2, true> inv;
+  inv.load(t & (T2 - 1));
+  // the kept bins, weighted and folded; the others are zero
+  row_sync<L>();
+  for (int k = t; k < n2; k += T) x[k] = make_float2(0.f, 0.f);
+  row_sync<L>();
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int k = index_of<L, true>(e, t);
+    const float h = dev::analytic_weight(k, n) * (1.0f / n);
+    if (k >= k_lo && k <= k_hi) x[k & (n2 - 1)] = make_float2(v[e].x * h, v[e].y * h);
   }
-  __syncthreads();
-  fft::transform_any<true>(x, log2ns);
-  const int nd = ns >> log2d;
-  const size_t out = (size_t)blockIdx.x * nd;
-  for (int m = threadIdx.x; m < nd; m += kPostThreads) {
-    const int k = m << log2d;
-    iq[out + m] = dev::cmul(x[fft::pad(k)], carrier(k, r_hi, r_lo));
+  row_sync<L>();
+  const int t2 = t & (T2 - 1);
+  float2 y[E2];
+#pragma unroll
+  for (int e = 0; e < E2; ++e) y[e] = x[index_of<L2, true>(e, t2)];
+  row_sync<L>();
+  transform<L2, true>(y, inv, x + (t / T2) * padded<L2>(), t2);
+  if (t >= T2 || rec >= rows) return;
+  const size_t out = (size_t)rec * n2;
+#pragma unroll
+  for (int e = 0; e < E2; ++e) {
+    const int m = index_of<L2, false>(e, t2);
+    iq[out + m] = cmul(y[e], carrier(m << LD, r_hi, r_lo));
+  }
+}
+
+template <int DT, int L>
+hipError_t launch_full(const void *rf, float2 *iq, int rows, float r_hi, float r_lo,
+                       hipStream_t stream) {
+  const int per = 2 * post_columns(L, post_block(L));
+  hipLaunchKernelGGL((k_iq_demod<DT, L>), dim3((rows + per - 1) / per), dim3(post_block(L)),
+                     dev::post_lds_bytes<L>(post_block(L)), stream, rf, iq, rows, r_hi, r_lo);
+  return hipGetLastError();
+}
+
+template <int DT, int L, int LD>
+hipError_t launch_decim(const void *rf, float2 *iq, int rows, int k_lo, int k_hi, float r_hi,
+                        float r_lo, hipStream_t stream) {
+  if constexpr (L > LD) {  // (a decimated record holds at least two samples)
+    const int per = post_columns(L, post_block(L));
+    hipLaunchKernelGGL((k_iq_demod_decim<DT, L, LD>), dim3((rows + per - 1) / per),
+                       dim3(post_block(L)), dev::post_lds_bytes<L>(post_block(L)), stream, rf, iq,
+                       rows, k_lo, k_hi, r_hi, r_lo);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int DT, int L>
+hipError_t launch_length(const void *rf, float2 *iq, int rows, float r_hi, float r_lo, int log2d,
+                         int k_lo, int k_hi, hipStream_t stream) {
+  switch (log2d) {
+    case 0: return launch_full<DT, L>(rf, iq, rows, r_hi, r_lo, stream);
+    case 1: return launch_decim<DT, L, 1>(rf, iq, rows, k_lo, k_hi, r_hi, r_lo, stream);
+    case 2: return launch_decim<DT, L, 2>(rf, iq, rows, k_lo, k_hi, r_hi, r_lo, stream);
+    case 3: return launch_decim<DT, L, 3>(rf, iq, rows, k_lo, k_hi, r_hi, r_lo, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int DT>
+hipError_t launch_type(const void *rf, float2 *iq, int rows, int log2ns, float r_hi, float r_lo,
+                       int log2d, int k_lo, int k_hi, hipStream_t stream) {
+  switch (log2ns) {
+#define PWBF_LEN(L) \
+  case L: return launch_length<DT, L>(rf, iq, rows, r_hi, r_lo, log2d, k_lo, k_hi, stream);
+    PWBF_LEN(1) PWBF_LEN(2) PWBF_LEN(3) PWBF_LEN(4) PWBF_LEN(5) PWBF_LEN(6) PWBF_LEN(7)
+    PWBF_LEN(8) PWBF_LEN(9) PWBF_LEN(10) PWBF_LEN(11) PWBF_LEN(12)
+#undef PWBF_LEN
+    default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
-size_t iq_demod_lds_bytes(int ns) { return fft::lds_bytes(ns, 1); }
-
 hipError_t launch_iq_demod(const void *rf, int dtype, void *iq, int rows, int log2ns, float r_hi,
                            float r_lo, int log2d, int k_lo, int k_hi, hipStream_t stream) {
-  const size_t lds = iq_demod_lds_bytes(1 << log2ns);
   float2 *out = (float2 *)iq;
-  if (log2d > 0) {
-    if (dtype == kI16)
-      hipLaunchKernelGGL(k_iq_demod_decim<kI16>, dim3(rows), dim3(kPostThreads), lds, stream, rf,
-                         out, log2ns, log2d, k_lo, k_hi, r_hi, r_lo);
-    else if (dtype == kF16)
-      hipLaunchKernelGGL(k_iq_demod_decim<kF16>, dim3(rows), dim3(kPostThreads), lds, stream, rf,
-                         out, log2ns, log2d, k_lo, k_hi, r_hi, r_lo);
-    else
-      hipLaunchKernelGGL(k_iq_demod_decim<kF32>, dim3(rows), dim3(kPostThreads), lds, stream, rf,
-                         out, log2ns, log2d, k_lo, k_hi, r_hi, r_lo);
-    return hipGetLastError();
-  }
-  const dim3 pairs((rows + 1) / 2);  // two records per block
   if (dtype == kI16)
-    hipLaunchKernelGGL(k_iq_demod<kI16>, pairs, dim3(kPostThreads), lds, stream, rf, out, rows,
-                       log2ns, r_hi, r_lo);
-  else if (dtype == kF16)
-    hipLaunchKernelGGL(k_iq_demod<kF16>, pairs, dim3(kPostThreads), lds, stream, rf, out, rows,
-                       log2ns, r_hi, r_lo);
-  else
-    hipLaunchKernelGGL(k_iq_demod<kF32>, pairs, dim3(kPostThreads), lds, stream, rf, out, rows,
-                       log2ns, r_hi, r_lo);
-  return hipGetLastError();
+    return launch_type<kI16>(rf, out, rows, log2ns, r_hi, r_lo, log2d, k_lo, k_hi, stream);
+  if (dtype == kF16)
+    return launch_type<kF16>(rf, out, rows, log2ns, r_hi, r_lo, log2d, k_lo, k_hi, stream);
+  return launch_type<kF32>(rf, out, rows, log2ns, r_hi, r_lo, log2d, k_lo, k_hi, stream);
 }
 
 }  // namespace pwbf

@@ -3,22 +3,27 @@
 // maximum), shared by the single-frame and the batched launches.
 #include <hip/hip_runtime.h>
 
-#include "fft_lds.h"
+#include <type_traits>
+
+#include "fft_reg.h"
 #include "frame_max.h"
 #include "plan.h"
+#include "post_layout.h"
 
 namespace pwbf {
 namespace dev {
 
-constexpr int kPostThreads = 256;
-static_assert(kPostThreads == fft::kThreads, "post-processing blocks run the block FFT");
-
-// LDS of one post-processing block: the padded column
-__host__ __device__ constexpr size_t post_lds_bytes(int nz) { return fft::lds_bytes(nz, 1); }
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+// LDS of a block of that many threads
+template <int L>
+__host__ __device__ constexpr size_t post_lds_bytes(int block_threads) {
+  return (size_t)fftr::padded<L>() * post_columns(L, block_threads) * 8;
 }
+// LDS of a batched block, whatever the length of its columns
+constexpr size_t kPostBatchLdsBytes = post_lds_bytes<12>(kPostThreads);
+static_assert(post_lds_bytes<3>(kPostThreads) == kPostBatchLdsBytes &&
+                  post_lds_bytes<2>(kPostThreads) <= kPostBatchLdsBytes &&
+                  post_lds_bytes<1>(kPostThreads) <= kPostBatchLdsBytes,
+              "");
 
 // One-sided weight of the analytic signal at bin k of n: 1 at DC and Nyquist,
 // 2 on positive bins, 0 on negative ones.
@@ -27,62 +32,85 @@ __device__ __forceinline__ float analytic_weight(int k, int n) {
   return (k == 0 || k == half_n) ? 1.f : (k < half_n ? 2.f : 0.f);
 }
 
-// Post-process column ix of the frame described by Q, with LDS at sm
-// (post_lds_bytes(nz)). LZ > 0: the column length is 2^LZ, known at compile
-// time (loop bounds and the transform fixed); LZ = 0: Q.log2nz at run time.
-template <int LZ = 0>
-__device__ __forceinline__ void postz_column(const PostPlan &Q, int ix, float2 *sm) {
-  const int L = LZ ? LZ : Q.log2nz, nz = 1 << L, half_n = nz >> 1;
-  float2 *x = sm;  // the column, padded layout
-  const int tid = threadIdx.x;
-  const float *src = Q.src + (size_t)ix * nz;
+// Largest m >= 0 of the wavefront, in lane 63. Lanes combine within rows of 16
+// by data-parallel moves, then rows 0 and 2 into 1 and 3, then 1 into 3 (a
+// shuffle is an LDS round trip, six of them in a row at the end of every
+// column).
+__device__ __forceinline__ float wave_max63(float m) {
+  auto step = [](float v, auto ctrl, auto rows) {
+    const int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value,
+                                              decltype(rows)::value, 0xf, false);
+    return fmaxf(v, __int_as_float(o));
+  };
+  using all = std::integral_constant<int, 0xf>;
+  m = step(m, std::integral_constant<int, 0x111>{}, all{});  // row_shr:1
+  m = step(m, std::integral_constant<int, 0x112>{}, all{});  // row_shr:2
+  m = step(m, std::integral_constant<int, 0x114>{}, all{});  // row_shr:4
+  m = step(m, std::integral_constant<int, 0x118>{}, all{});  // row_shr:8
+  m = step(m, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  m = step(m, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  return m;
+}
 
-  for (int k = tid; k < nz; k += kPostThreads) x[fft::pad(k)] = make_float2(src[k], 0.f);
-  __syncthreads();
-  if constexpr (LZ > 0)
-    fft::transform<LZ, false>(x);
-  else
-    fft::transform_any<false>(x, L);
+// Post-process columns ix0, ix0 + 1, ... of the frame described by Q, of 2^L
+// samples each, one per thread group of the block (post_columns of them; those
+// past the last column of the frame do nothing), with LDS at sm.
+template <int L>
+__device__ __forceinline__ void postz_columns(const PostPlan &Q, int ix0, float2 *sm) {
+  using namespace fftr;
+  constexpr int n = 1 << L, T = threads(L), E = points(L);
+  const int row = (int)threadIdx.x / T, t = (int)threadIdx.x & (T - 1);
+  float2 *x = sm + row * padded<L>();
+  const int ix = ix0 + row;
+  const bool mine = ix < Q.nx;
+  const size_t base = (size_t)min(ix, Q.nx - 1) * n;
 
+  float2 v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = make_float2(Q.src[base + index_of<L, false>(e, t)], 0.f);
   // analytic-signal weights, band mask, and the 1/nz of the inverse
-  const float inv_n = 1.0f / (float)nz;
-  for (int k = tid; k < nz; k += kPostThreads) {
-    float h = analytic_weight(k, nz);
-    if (Q.bandpass) {
-      const int ak = k <= half_n ? k : nz - k;
-      if (ak < Q.k_lo || ak > Q.k_hi) h = 0.f;
-    }
-    const float2 v = x[fft::pad(k)];
-    x[fft::pad(k)] = make_float2(v.x * h * inv_n, v.y * h * inv_n);
-  }
-  __syncthreads();
-  if constexpr (LZ > 0)
-    fft::transform<LZ, true>(x);
-  else
-    fft::transform_any<true>(x, L);
+  const bool band = Q.bandpass;
+  const int k_lo = Q.k_lo, k_hi = Q.k_hi;
+  filter<L>(v, x, t, [&](int k) __attribute__((always_inline)) {
+    const float h = analytic_weight(k, n) * (1.0f / n);
+    const int ak = k <= n / 2 ? k : n - k;
+    return band && (ak < k_lo || ak > k_hi) ? 0.f : h;
+  });
 
   float m = 0.f;
-  for (int k = tid; k < nz; k += kPostThreads) {
-    const float2 z = x[fft::pad(k)];
-    const size_t o = (size_t)ix * nz + k;
-    if (Q.filtered) Q.filtered[o] = z.x;
-    const float e = sqrtf(z.x * z.x + z.y * z.y);
-    if (Q.env) Q.env[o] = e;
-    m = fmaxf(m, e);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const size_t o = base + index_of<L, false>(e, t);
+    const float a = sqrtf(v[e].x * v[e].x + v[e].y * v[e].y);
+    if (mine) {
+      if (Q.filtered) Q.filtered[o] = v[e].x;
+      if (Q.env) Q.env[o] = a;
+      m = fmaxf(m, a);
+    }
   }
   if (Q.ws_max) {
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    __shared__ float wmax[kPostThreads / 64];
-    if ((tid & 63) == 0) wmax[tid >> 6] = m;
-    __syncthreads();
-    if (tid == 0) {
-      float bm = wmax[0];
-      for (int i = 1; i < kPostThreads / 64; ++i) bm = fmaxf(bm, wmax[i]);
-      frame_max_fold(Q.ws_max, bm);
-    }
+    m = wave_max63(m);
+    if (((int)threadIdx.x & 63) == 63) frame_max_fold(Q.ws_max, m);
   }
 }
 
+// the same for a column length known only at run time (uniform over the block)
+__device__ __forceinline__ void postz_columns_any(const PostPlan &Q, int ix0, float2 *sm) {
+  switch (Q.log2nz) {
+    case 1: postz_columns<1>(Q, ix0, sm); break;
+    case 2: postz_columns<2>(Q, ix0, sm); break;
+    case 3: postz_columns<3>(Q, ix0, sm); break;
+    case 4: postz_columns<4>(Q, ix0, sm); break;
+    case 5: postz_columns<5>(Q, ix0, sm); break;
+    case 6: postz_columns<6>(Q, ix0, sm); break;
+    case 7: postz_columns<7>(Q, ix0, sm); break;
+    case 8: postz_columns<8>(Q, ix0, sm); break;
+    case 9: postz_columns<9>(Q, ix0, sm); break;
+    case 10: postz_columns<10>(Q, ix0, sm); break;
+    case 11: postz_columns<11>(Q, ix0, sm); break;
+    default: postz_columns<12>(Q, ix0, sm); break;
+  }
+}
 
 // 20 log10(env / max), clipped at the floor (the floor everywhere when max is 0);
 // a true division, so the maximum itself maps to exactly 0 dB

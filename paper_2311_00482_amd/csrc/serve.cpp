@@ -24,6 +24,7 @@
 #include "frame_max.h"
 #include "metrics.h"
 #include "plan_host.h"
+#include "post_layout.h"
 #include "serve.h"
 #include "serve_core.h"
 
@@ -56,7 +57,7 @@ struct Probe {
   GeomCopy geom;
   int want_env = 0, want_log = 0, want_quality = 0;
   size_t rf_elems = 0;
-  int tiles = 0, cols = 0, log_cols = 0;
+  int tiles = 0, col_blocks = 0, log_cols = 0;
 };
 
 struct Slot {
@@ -134,7 +135,7 @@ struct pwbf_server {
   std::vector<int> plan_class;             // tile class of each slot's plan
   int class_blocks[pwbf::kTileClasses] = {};  // persistent blocks per class
   hipStream_t copy_s[kCopyStreams] = {}, comp_s = nullptr;
-  int device = 0, lds = 0, max_nz = 0;
+  int device = 0, lds = 0;
   std::unique_ptr<pwbf::serve::Core> core;
   std::unique_ptr<HipLauncher> launcher;
   std::thread worker;
@@ -216,7 +217,7 @@ int HipLauncher::launch(const pwbf::serve::Batch &batch, std::string *err) {
     const Probe &p = s_->probes[s_->slots[slot].probe];
     al.plan[k] = slot;
     al.tile0[k + 1] = al.tile0[k] + p.tiles;
-    al.col0[k + 1] = al.col0[k] + p.cols;
+    al.col0[k + 1] = al.col0[k] + p.col_blocks;
     al.log0[k + 1] = al.log0[k] + p.log_cols;
     arg->ids.push_back(batch[k].first);
     if (p.want_quality) {
@@ -234,7 +235,7 @@ int HipLauncher::launch(const pwbf::serve::Batch &batch, std::string *err) {
     if (e == hipSuccess) e = hipStreamWaitEvent(s_->comp_s, s_->slots[r.second].uploaded, 0);
   if (e == hipSuccess)
     e = pwbf::launch_serve(s_->d_plans, s_->d_post, al, s_->plan_class.data(), s_->class_blocks,
-                           s_->d_counter, s_->lds, s_->max_nz, s_->comp_s);
+                           s_->d_counter, s_->lds, s_->comp_s);
   if (e == hipSuccess && ql.n > 0) {
     const size_t off = (size_t)arg->region * pwbf::serve::Core::kMaxBatch;
     e = pwbf::launch_quality(s_->d_quality, ql, s_->d_qout + off,
@@ -418,13 +419,13 @@ int pwbf_server_create(const pwbf_probe *probes, int32_t n, size_t hbm_budget_by
         pwbf::quality_chunks(qp.out, &qp.chunks_out, &qp.cols_out);
       }
       p.tiles = P.n_tiles;
-      p.cols = pwbf::post_needed(&o) ? g.nx : 0;
+      const int run = pwbf::post_needed(&o) ? pwbf::post_columns(Q.log2nz, pwbf::kPostThreads) : 1;
+      p.col_blocks = pwbf::post_needed(&o) ? (g.nx + run - 1) / run : 0;
       p.log_cols = p.want_log ? g.nx : 0;
       if (k == 0)  // its deepest (first-run) tile row holds the costliest tiles
         for (int t = 0; t < P.n_tiles; ++t)
           info[i].tile_cost = std::max(info[i].tile_cost, pwbf::tile_cost(&g, P, t));
       s->lds = std::max(s->lds, (int)pwbf::plan_lds_bytes(P));
-      if (pwbf::post_needed(&o)) s->max_nz = std::max(s->max_nz, g.nz);
       info[i].slots.push_back(idx);
       plans.push_back(P);
       post.push_back(Q);

@@ -14,7 +14,7 @@ struct ActiveList {
   int n;                           // active slots in this batch
   int plan[kServeMaxActive];       // plan / post table index of each
   int tile0[kServeMaxActive + 1];  // prefix sums of tiles
-  int col0[kServeMaxActive + 1];   // prefix sums of post-processed columns
+  int col0[kServeMaxActive + 1];   // prefix sums of post-processing blocks (post_layout.h)
   int log0[kServeMaxActive + 1];   // prefix sums of log-image columns
 };
 
@@ -26,6 +26,6 @@ hipError_t launch_i16_to_f16(void *buf, size_t n, hipStream_t stream);
 // (host arrays); counters: kTileClasses device words
 hipError_t launch_serve(const FramePlan *plans, const PostPlan *post, const ActiveList &al,
                         const int *plan_class, const int *class_blocks, int *counters,
-                        size_t lds, int max_nz, hipStream_t stream);
+                        size_t lds, hipStream_t stream);
 
 }  // namespace pwbf

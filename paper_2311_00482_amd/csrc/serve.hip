@@ -84,12 +84,13 @@ __global__ void __launch_bounds__(kWave * kServeWaves)
   X(16) X(17) X(18) X(19) X(20) X(21) X(22) X(23)
 static_assert(kTileClasses == 24, "one kernel per class");
 
-__global__ void __launch_bounds__(dev::kPostThreads)
+__global__ void __launch_bounds__(kPostThreads) __attribute__((amdgpu_waves_per_eu(4)))
     k_serve_postz(const PostPlan *__restrict__ post, const ActiveList al) {
   extern __shared__ __align__(16) float2 sm[];
   const int b = blockIdx.x;
   const int k = find_slot(al.col0, al.n, b);
-  dev::postz_column(post[al.plan[k]], b - al.col0[k], sm);
+  const PostPlan &Q = post[__builtin_amdgcn_readfirstlane(al.plan[k])];
+  dev::postz_columns_any(Q, (b - al.col0[k]) * post_columns(Q.log2nz, kPostThreads), sm);
 }
 
 __global__ void __launch_bounds__(256) k_serve_logc(const PostPlan *__restrict__ post,
@@ -130,7 +131,7 @@ hipError_t launch_i16_to_f16(void *buf, size_t n, hipStream_t stream) {
 
 hipError_t launch_serve(const FramePlan *plans, const PostPlan *post, const ActiveList &al,
                         const int *plan_class, const int *class_blocks, int *counters,
-                        size_t lds, int max_nz, hipStream_t stream) {
+                        size_t lds, hipStream_t stream) {
   hipLaunchKernelGGL(k_serve_reset, dim3((std::max(al.n, kTileClasses) + 255) / 256), dim3(256),
                      0, stream, counters, post, al);
   hipError_t e = hipGetLastError();
@@ -161,9 +162,8 @@ hipError_t launch_serve(const FramePlan *plans, const PostPlan *post, const Acti
     if (e != hipSuccess) return e;
   }
   if (al.col0[al.n] > 0) {
-    const size_t plds = dev::post_lds_bytes(max_nz);
-    hipLaunchKernelGGL(k_serve_postz, dim3(al.col0[al.n]), dim3(dev::kPostThreads), plds, stream,
-                       post, al);
+    hipLaunchKernelGGL(k_serve_postz, dim3(al.col0[al.n]), dim3(kPostThreads),
+                       dev::kPostBatchLdsBytes, stream, post, al);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
