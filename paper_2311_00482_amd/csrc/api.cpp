@@ -229,7 +229,7 @@ int pwbf_describe_plan(const pwbf_geometry *g, int32_t mode, int32_t angle,
   info->off_r = P.off_r;
   info->tiles_z = P.tiles_z;
   info->tiles_x = P.tiles_x;
-  info->threads_per_block = pwbf::kWave * P.wz * P.wx;
+  info->threads_per_block = pwbf::kWave * P.wz * P.wx * P.wc;
   info->blocks = P.n_tiles;
   info->n_angles_used = P.n_angles;
   info->lds_bytes = (int64_t)pwbf::plan_lds_bytes(P);

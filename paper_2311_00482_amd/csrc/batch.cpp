@@ -202,6 +202,7 @@ int pwbf_tune(const pwbf_geometry *g, const void *rf, int32_t rf_dtype, int32_t 
     if (pwbf::build_plan(g, rf, rf_dtype, mode, angle, &t, out, nullptr, 0, &Q, &err)) continue;
     if (waves && Q.wz * Q.wx != waves) continue;
     if (compact_only && !pwbf::root_compact(g, Q)) continue;
+    if (!waves) Q.wc = pwbf::choose_share(Q);  // as the tuned plan will
     hipError_t e = pwbf::launch_beamform(Q, s);  // warm-up
     for (int k = 0; k < 3 && e == hipSuccess; ++k) {
       if (k == 0) e = hipEventRecord(e0, s);

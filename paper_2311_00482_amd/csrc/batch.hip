@@ -54,9 +54,9 @@ __global__ void __launch_bounds__(kWave * kBatchWaves)
   const int tz = tile / P.tiles_x, tx = tile - tz * P.tiles_x;
   // the tile's channel hull, computed on the host (w.z, w.w)
   if constexpr (AB == 3)
-    dev::process_tile<kBatchMaxAngles, true, MODE, ONEGRP>(P, tz, tx, smem, w.z, w.w);
+    dev::process_tile<kBatchMaxAngles, true, MODE, ONEGRP ? dev::kOneGroup : dev::kGroups>(P, tz, tx, smem, w.z, w.w);
   else
-    dev::process_tile<AB == 0 ? 1 : (AB == 1 ? 5 : 11), false, MODE, ONEGRP>(P, tz, tx, smem,
+    dev::process_tile<AB == 0 ? 1 : (AB == 1 ? 5 : 11), false, MODE, ONEGRP ? dev::kOneGroup : dev::kGroups>(P, tz, tx, smem,
                                                                              w.z, w.w);
 }
 

@@ -7,6 +7,8 @@
 // consecutive addresses and the image writes are contiguous runs. With cpw > 1
 // a wavefront is split into cpw lane groups that share the same pixels and
 // divide the channels; their partial sums are reduced across lanes at the end.
+// With wc > 1 the block holds wc wavefronts for each of its wavefronts of pixels,
+// which divide the channels further and add their sums through LDS.
 //
 // For every chunk of channels the block stages, per (channel, angle), a window
 // of RF samples that covers every delay of every pixel of the tile, as pairs
@@ -350,6 +352,8 @@ __device__ __forceinline__ float uniform(float v) {
 }
 __device__ __forceinline__ ff uniform(ff v) { return {uniform(v.hi), uniform(v.lo)}; }
 
+enum Group : int { kGroups = 0, kOneGroup = 1, kShared = 2 };
+
 constexpr int kIqAhead = 4;  // IQ modes: window entries of a pixel read ahead
 
 // a compile-time flag handed to the generic lambdas of the channel loop
@@ -358,7 +362,10 @@ template <bool B> struct Flag { static constexpr bool value = B; };
 // AM: angles handled per pixel; PRED: AM is an upper bound and angles >= A are
 // skipped (17..32 angles of the IQ modes, batch and serving frames of other than
 // 1, 5 and 11 angles), else exactly AM == A angles, fully unrolled.
-// ONEGRP: one lane group per wavefront (cpw == 1), so the LDS window of a
+// GROUP: kGroups, any lane groups per wavefront and wavefronts per pixel;
+// kOneGroup, one of each; kShared, one lane group (cpw == 1) and any wavefronts
+// per pixel (a stride of channels that the compiler does not know costs the
+// 11-angle DAS loop 15%). With one lane group the LDS window of a
 // channel is the same for the whole wavefront and its address stays scalar.
 // SEL: the apodization weight carries the aperture test (needed for boxcar).
 //
@@ -384,7 +391,7 @@ template <bool B> struct Flag { static constexpr bool value = B; };
 // change to the windows.
 // hull_lo >= 0: the tile's channel hull [hull_lo, hull_hi) comes from the
 // caller (the batch computes it on the host); else the block finds it.
-template <int AM, bool PRED, int MODE, bool ONEGRP, bool SEL>
+template <int AM, bool PRED, int MODE, int GROUP, bool SEL>
 __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, int tx,
                                                   unsigned char *smem, int hull_lo = -1,
                                                   int hull_hi = -1) {
@@ -404,14 +411,21 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform
-  const int cpw = ONEGRP ? 1 : P.cpw;
+  constexpr bool ONEGRP = GROUP != kGroups;
+  const int cpw = ONEGRP ? 1 : P.cpw, wc = GROUP == kOneGroup ? 1 : P.wc;
   const int ppw = kWave / cpw;  // lanes per group
   const int pl = lane & (ppw - 1), grp = ONEGRP ? 0 : lane / ppw;
   const int lz = P.lz, lx = P.lx;  // a group's pixels: lz along depth by lx along x
-  // wave / wz for wave < 8 and wz <= 8 through a float reciprocal ((wave + 0.5) /
-  // wz lies at least 1 / 16 from an integer); lz is a power of two
-  const int wxi = (int)((wave + 0.5f) * __builtin_amdgcn_rcpf((float)P.wz));
-  const int wzi = wave - wxi * P.wz;
+  // wave / (wz wx) and the rest / wz for wave < 8 through float reciprocals
+  // ((wave + 0.5) / wz lies at least 1 / 16 from an integer); lz is a power of two.
+  // Wavefronts wcg = 0..wc-1 of the same pixels share their channels.
+  const int nwp = P.wz * P.wx;
+  const int wcg = GROUP == kOneGroup ? 0
+                                     : __builtin_amdgcn_readfirstlane((int)(
+                                           (wave + 0.5f) * __builtin_amdgcn_rcpf((float)nwp)));
+  const int wpix = wave - wcg * nwp;
+  const int wxi = (int)((wpix + 0.5f) * __builtin_amdgcn_rcpf((float)P.wz));
+  const int wzi = wpix - wxi * P.wz;
   const int lzs = __builtin_ctz(lz);
   const int TZ = P.tile_z, TX = P.tile_x;
   const int iz0 = tz * TZ, ix0 = tx * TX;
@@ -464,65 +478,51 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   // span below Z_max / (2 F#). The test carries a 1e-3 relative margin, so
   // float rounding can only add a channel, never drop one; outputs are those
   // of the loop over all channels.
-  __shared__ int s_erange[2 * kMaxWavesPerBlock];
+  __shared__ unsigned long long s_active[kMaxChannels / kWave];  // bit per channel
   const bool given_hull = hull_lo >= 0;
+  const bool find_hull = P.apod != kNone && !given_hull;
 
-  // The channel table: per channel the window origin LR and, except for DMAS
-  // and pDAS, the reference delay rx(q) in float-float and the terms of the
-  // receive-delay difference. It normally holds every channel (of a given hull:
-  // every one of the hull) and is filled once, beside the hull search and the
-  // angle constants and by other wavefronts than those; where the LDS does not
-  // hold it beside a window chunk, it is filled again every P.tab channels.
-  // Entries past the last channel (padding of several lane groups) repeat it.
-  auto fill_table = [&](int base, int n) __attribute__((always_inline)) {
-    const int bs = (int)blockDim.x, half = (bs >> 1) & -kWave;
-    for (int c = tid >= half ? tid - half : tid + bs - half; c < n; c += bs) {
-      const int e = min(base + c, N - 1);
+  // The channel pass, a thread per channel: the aperture test and the channel
+  // table, per channel the window origin LR and, except for DMAS and pDAS, the
+  // reference delay rx(q) in float-float and the terms of the receive-delay
+  // difference. The table normally holds every channel (of a given hull: every
+  // one of the hull) and is filled once; where the LDS does not hold it beside a
+  // window chunk, it is filled again every P.tab channels. Entries past the last
+  // channel (padding of several lane groups) repeat it.
+  auto channel_pass = [&](int base, int n, bool table, bool hull) __attribute__((always_inline)) {
+    for (int c0 = wave * kWave; c0 < n; c0 += (int)blockDim.x) {
+      const int c = c0 + lane, e = min(base + c, N - 1);
       const ff xe = {P.xe[e], P.xel[e]};
       const ff dq = ff_add(Xq, ff_neg(xe));
       const float dqf = ff_f(dq);
-      const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
-      s_lr[c] = (int)lr;
-      if constexpr (!WREF) {
-        const ff rq2 = ff_add(ff_mul(dq, dq), ff_mul(Zq, Zq));
-        const ff rq = ff_sqrt(rq2);
-        s_ch[c] = make_float4(dqf, ff_f(rq2), ff_f(rq) + 1e-20f,
-                              ff_f(ff_add(rq, {-(lr + (float)P.off_r), 0.f})));
+      if (hull) {
+        const float zmax = Zqf + dzhi;
+        const float ddx = fmaxf(fmaxf(dqf + dxlo, -(dqf + dxhi)), 0.f);
+        const unsigned long long m =
+            __ballot(c < N && zmax > 0.f && ddx * P.ap_k < zmax * 1.001f);
+        if (lane == 0 && c0 < N) s_active[c0 / kWave] = m;
       }
-      if constexpr (IQ) s_ph[c] = carrier_phasor((int)lr + P.off_r, P.iq_r, P.iq_rl);
+      if (table && c < n) {
+        const float lr = window_lr(dqf, dxlo, dxhi, Zqf + dzlo, Zqf + dzhi);
+        s_lr[c] = (int)lr;
+        if constexpr (!WREF) {
+          const ff rq2 = ff_add(ff_mul(dq, dq), ff_mul(Zq, Zq));
+          const ff rq = ff_sqrt(rq2);
+          s_ch[c] = make_float4(dqf, ff_f(rq2), ff_f(rq) + 1e-20f,
+                                ff_f(ff_add(rq, {-(lr + (float)P.off_r), 0.f})));
+        }
+        if constexpr (IQ) s_ph[c] = carrier_phasor((int)lr + P.off_r, P.iq_r, P.iq_rl);
+      }
     }
   };
   int e_tab = given_hull ? __builtin_amdgcn_readfirstlane(hull_lo) : 0;
   const int tab_all = (given_hull ? __builtin_amdgcn_readfirstlane(hull_hi) : N) - e_tab + cpw - 1;
   const bool tab_once = tab_all <= P.tab;
-  if (tab_once) fill_table(e_tab, tab_all);
-  if (P.apod != kNone && !given_hull) {
-    const float zmax = Zqf + dzhi;
-    int lo = N, hi = 0;
-    for (int e = tid; e < N; e += blockDim.x) {
-      const float dq = ff_f(ff_add(Xq, ff_neg({P.xe[e], P.xel[e]})));
-      const float ddx = fmaxf(fmaxf(dq + dxlo, -(dq + dxhi)), 0.f);
-      if (zmax > 0.f && ddx * P.ap_k < zmax * 1.001f) {
-        lo = min(lo, e);
-        hi = max(hi, e + 1);
-      }
-    }
-    // only wavefronts whose threads hold a channel (wave * 64 < N) reduce
-    if (wave * kWave < N) {
-      for (int off = 1; off < kWave; off <<= 1) {
-        lo = min(lo, __shfl_xor(lo, off));
-        hi = max(hi, __shfl_xor(hi, off));
-      }
-      if (lane == 0) {
-        s_erange[2 * wave] = lo;
-        s_erange[2 * wave + 1] = hi;
-      }
-    }
-  }
+  if (tab_once || find_hull) channel_pass(e_tab, tab_all, tab_once, find_hull);
 
   // Per-angle tile constants: window origin LT = floor(min_tile tx) - 1 and
   // tx(q) - LT. tx is linear, so its tile minimum is at a corner. Angle a is
-  // taken by thread blockDim - 1 - a: another wavefront than the aperture hull
+  // taken by thread blockDim - 1 - a: another wavefront than the channel pass
   // above, which starts at thread 0, so the two run side by side.
   for (int a = (int)blockDim.x - 1 - tid; a < A; a += blockDim.x) {
     const ff sa = {P.sa[a], P.sal[a]}, ca = {P.ca[a], P.cal[a]}, to = {P.to[a], P.tol[a]};
@@ -539,13 +539,15 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   if (given_hull) {
     e_lo = __builtin_amdgcn_readfirstlane(hull_lo);
     e_hi = __builtin_amdgcn_readfirstlane(hull_hi);
-  } else if (P.apod != kNone) {
+  } else if (find_hull) {
     e_hi = 0;
     e_lo = N;
-    const int nwr = min((int)(blockDim.x / kWave), (N + kWave - 1) / kWave);
-    for (int w = 0; w < nwr; ++w) {
-      e_lo = min(e_lo, s_erange[2 * w]);
-      e_hi = max(e_hi, s_erange[2 * w + 1]);
+    for (int w = 0; w * kWave < N; ++w) {
+      const unsigned long long m = s_active[w];
+      if (m) {
+        e_lo = min(e_lo, w * kWave + (int)__builtin_ctzll(m));
+        e_hi = w * kWave + kWave - (int)__builtin_clzll(m);
+      }
     }
     e_lo = __builtin_amdgcn_readfirstlane(e_lo);
     e_hi = __builtin_amdgcn_readfirstlane(e_hi);
@@ -594,7 +596,7 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     const int cnt_pad = ONEGRP ? cnt : (cnt + cpw - 1) / cpw * cpw;  // rows read
     if (!tab_once && (e0 == e_lo || e0 + cnt_pad > e_tab + P.tab)) {
       e_tab = e0;
-      fill_table(e0, min(P.tab, e_hi - e0 + cpw - 1));
+      channel_pass(e0, min(P.tab, e_hi - e0 + cpw - 1), true, false);
       __syncthreads();
     }
     const int ct = e0 - e_tab;  // the chunk's first channel in the table
@@ -769,15 +771,16 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     // (one channel is a chain of two dependent LDS round trips, and a small
     // grid leaves few wavefronts per SIMD to hide them)
     auto channels = [&](auto sq) __attribute__((always_inline)) {
+      const int step = cpw * wc;
+      int k = wcg * cpw;
       if constexpr (AM <= 2 && !PRED) {
-        int k = 0;
-        for (; k + cpw < cnt; k += 2 * cpw) {
+        for (; k + step < cnt; k += 2 * step) {
           channel(k, sq);
-          channel(k + cpw, sq);
+          channel(k + step, sq);
         }
         if (k < cnt) channel(k, sq);
       } else {
-        for (int k = 0; k < cnt; k += cpw) channel(k, sq);
+        for (; k < cnt; k += step) channel(k, sq);
       }
     };
     if constexpr (MODE == kPdas) {
@@ -790,6 +793,48 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     }
   }
 
+  // Sums over the lane groups of a wavefront, then over the wavefronts that share
+  // its pixels (through the LDS of the windows, which have been read; value i of
+  // plan_sums(P) values), complete in the lanes that write the pixel.
+  const bool shared = GROUP == kOneGroup ? false : wc > 1;
+  float *s_sum = (float *)s_pairs;
+  auto group_sum = [&](float v) __attribute__((always_inline)) {
+    for (int off = ppw; off < kWave; off <<= 1) v += __shfl_xor(v, off);
+    return v;
+  };
+  auto put_sum = [&](int i, float v) __attribute__((always_inline)) {
+    s_sum[(i * nwp * wc + wave) * kWave + lane] = v;
+  };
+  auto get_sum = [&](int i, float v) __attribute__((always_inline)) {
+    if (shared) {
+      v = 0.f;
+      for (int w = 0; w < wc; ++w)
+        v += s_sum[(i * nwp * wc + wpix + w * nwp) * kWave + lane];
+    }
+    return v;
+  };
+  if (shared) {
+    __syncthreads();
+    if constexpr (MODE == kDas) {
+      put_sum(0, group_sum(total));
+    } else {
+#pragma unroll
+      for (int a = 0; a < AM; ++a) {
+        if (!PRED || a < A) {
+          put_sum(a, group_sum(S[a]));
+          if constexpr (IQ) put_sum(A + a, group_sum(SI[a]));
+        }
+      }
+      if constexpr (MODE == kDmas) put_sum(A, group_sum(Q));
+    }
+    __syncthreads();
+  }
+  // the sum of v over the lanes and wavefronts of the pixel, value i
+  auto pixel_sum = [&](int i, float v) __attribute__((always_inline)) {
+    return shared ? get_sum(i, v) : group_sum(v);
+  };
+  const bool mine = wcg == 0 && grp == 0 && ix < P.nx && iz < P.nz;
+
   if constexpr (IQ) {
     // per angle: the transmit phasor exp(2 pi i r (LT + off_t + tx(p) - LT - off_t))
     // times the angle's sum; BB-DMAS squares it; the angles add
@@ -797,11 +842,7 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
 #pragma unroll
     for (int a = 0; a < AM; ++a) {
       if (!PRED || a < A) {
-        float tr = S[a], ti = SI[a];
-        for (int off = ppw; off < kWave; off <<= 1) {
-          tr += __shfl_xor(tr, off);
-          ti += __shfl_xor(ti, off);
-        }
+        const float tr = pixel_sum(a, S[a]), ti = pixel_sum(A + a, SI[a]);
         const float2 tp = s_tph[a];
         const float rho = P.iq_r * txl[a];
         const float ct = __builtin_amdgcn_cosf(rho), st = __builtin_amdgcn_sinf(rho);
@@ -816,7 +857,6 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
         }
       }
     }
-    const bool mine = grp == 0 && ix < P.nx && iz < P.nz;
     const float env = sqrtf(yr * yr + yi * yi);
     if (mine) {
       const size_t o = (size_t)ix * P.nz + iz;
@@ -840,35 +880,31 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
 
   float y;
   if constexpr (MODE == kDas) {
-    for (int off = ppw; off < kWave; off <<= 1) total += __shfl_xor(total, off);
-    y = total;
+    y = pixel_sum(0, total);
   } else if constexpr (MODE == kPdas) {
     // per angle the signed p-th power of the summed roots; the angles add
     y = 0.f;
 #pragma unroll
     for (int a = 0; a < AM; ++a) {
       if (!PRED || a < A) {
-        float t = S[a];
-        for (int off = ppw; off < kWave; off <<= 1) t += __shfl_xor(t, off);
+        const float t = pixel_sum(a, S[a]);
         y += P.pdas_p == 2.0f
                  ? t * fabsf(t)
                  : copysignf(__builtin_amdgcn_exp2f(P.pdas_p * __builtin_amdgcn_logf(fabsf(t))), t);
       }
     }
   } else {
-    for (int off = ppw; off < kWave; off <<= 1) Q += __shfl_xor(Q, off);
     float sq = 0.f;
 #pragma unroll
     for (int a = 0; a < AM; ++a) {
       if (!PRED || a < A) {
-        float s = S[a];
-        for (int off = ppw; off < kWave; off <<= 1) s += __shfl_xor(s, off);
+        const float s = pixel_sum(a, S[a]);
         sq = fmaf(s, s, sq);
       }
     }
-    y = 0.5f * (sq - Q);
+    y = 0.5f * (sq - pixel_sum(A, Q));
   }
-  if (grp == 0 && ix < P.nx && iz < P.nz) P.out[(size_t)ix * P.nz + iz] = y;
+  if (mine) P.out[(size_t)ix * P.nz + iz] = y;
 }
 
 // The tile body for plan P. The exact-angle RF kernels of one lane group
@@ -876,17 +912,17 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
 // two fewer instructions per (pixel, channel); every other kernel and boxcar
 // apodization take the general one. (The serve kernels call the general body
 // directly: there the second body costs registers.)
-template <int AM, bool PRED, int MODE, bool ONEGRP>
+template <int AM, bool PRED, int MODE, int GROUP>
 __device__ __forceinline__ void process_tile(const FramePlan &P, int tz, int tx,
                                              unsigned char *smem, int hull_lo = -1,
                                              int hull_hi = -1) {
-  if constexpr ((MODE == kDas || MODE == kDmas || MODE == kPdas) && ONEGRP && !PRED) {
+  if constexpr ((MODE == kDas || MODE == kDmas || MODE == kPdas) && GROUP != kGroups && !PRED) {
     if (P.apod != kBoxcar) {
-      process_tile_body<AM, PRED, MODE, ONEGRP, false>(P, tz, tx, smem, hull_lo, hull_hi);
+      process_tile_body<AM, PRED, MODE, GROUP, false>(P, tz, tx, smem, hull_lo, hull_hi);
       return;
     }
   }
-  process_tile_body<AM, PRED, MODE, ONEGRP, true>(P, tz, tx, smem, hull_lo, hull_hi);
+  process_tile_body<AM, PRED, MODE, GROUP, true>(P, tz, tx, smem, hull_lo, hull_hi);
 }
 
 }  // namespace dev

@@ -24,7 +24,7 @@ namespace {
 // wavefronts, the entries read kIqAhead at a time) instead of 108 (four).
 constexpr int min_waves(int am, int mode) { return am <= (is_iq_mode(mode) ? 11 : 16) ? 6 : 4; }
 
-template <int AM, bool PRED, int MODE, bool ONEGRP>
+template <int AM, bool PRED, int MODE, int GROUP>
 __global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
     __attribute__((amdgpu_waves_per_eu(min_waves(AM, MODE)))) k_beamform(const FramePlan P) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -34,18 +34,20 @@ __global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
   if (!is_iq_mode(MODE) && P.ws_max && b == 0) dev::frame_max_clear(P.ws_max, threadIdx.x);
   const int q = b / P.tiles_x;
   const int tz = P.tiles_z - 1 - q, tx = b - q * P.tiles_x;
-  dev::process_tile<AM, PRED, MODE, ONEGRP>(P, tz, tx, smem);
+  dev::process_tile<AM, PRED, MODE, GROUP>(P, tz, tx, smem);
 }
 
 template <int AM, bool PRED, int MODE>
 hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
-  const dim3 block(kWave * P.wz * P.wx);
+  const dim3 block(kWave * P.wz * P.wx * P.wc);
   const dim3 grid(P.n_tiles);
   const size_t lds = plan_lds_bytes(P);
-  if (P.cpw == 1)
-    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, true>), grid, block, lds, stream, P);
+  if (P.cpw > 1)
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups>), grid, block, lds, stream, P);
+  else if (P.wc > 1)
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kShared>), grid, block, lds, stream, P);
   else
-    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, false>), grid, block, lds, stream, P);
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kOneGroup>), grid, block, lds, stream, P);
   return hipGetLastError();
 }
 

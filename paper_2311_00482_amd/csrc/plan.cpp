@@ -182,9 +182,7 @@ int validate_outputs(const pwbf_geometry *g, const pwbf_outputs *o, void *ws, si
 // layout (~10% faster with an earlier kernel; with the current one the two
 // shapes time within 0.5% on every benchmark workload). Small frames split channels
 // across lane groups so there are enough waves.
-pwbf_tile default_tile(const pwbf_geometry *g, int n_angles_used, int mode) {
-  (void)mode;
-  (void)n_angles_used;
+pwbf_tile default_tile(const pwbf_geometry *g) {
   pwbf_tile t;
   int64_t pixels = (int64_t)g->nx * g->nz;
   t.cpw = pixels >= 256 * 1024 ? 1 : (pixels >= 64 * 1024 ? 2 : 4);
@@ -200,6 +198,60 @@ pwbf_tile default_tile(const pwbf_geometry *g, int n_angles_used, int mode) {
   t.wx = t.cpw == 1 ? 2 : 8;
   t.chunk = 0;
   return t;
+}
+
+// Wavefronts of a single frame's launch, up to which those of a tile are doubled
+// by sharing its pixels' channels (wc). One or two angles are bound by latency: a
+// wavefront that shares a pixel's channels halves its chain of LDS round trips
+// (256 x 512 DAS of 64 channels 10.0 -> 7.7 us at two per pixel, 8.3 and more at
+// four; 128 x 256 6.6 -> 6.0; a 58 x 26 preview 9.9 -> 5.0). From three angles
+// on the windows in LDS limit the blocks of a CU, and sharing puts more
+// wavefronts on each.
+static int64_t wave_target(int n_angles, int mode) {
+  return n_angles >= 3 && !is_iq_mode(mode) ? 8200 : 4500;
+}
+static int max_share(int mode) {  // each wavefront of a root mode fills a table of its own
+  return wave_ref_mode(mode) ? 4 : 8;
+}
+
+// The default shape of a single frame: tiles 16 pixels deep of 16 x 4-pixel
+// wavefronts, the fewer of them the more wavefronts are to share their channels;
+// 2 x 2 of 8 x 8 where none do, and from a million pixels on the shape of
+// default_tile.
+static pwbf_tile single_tile(const pwbf_geometry *g, int n_angles, int mode) {
+  const int64_t pixels = (int64_t)g->nx * g->nz;
+  if (pixels >= 1024 * 1024) return default_tile(g);
+  const int64_t waves = (pixels + kWave - 1) / kWave, target = wave_target(n_angles, mode);
+  if (waves * 8 <= target && max_share(mode) >= 8) return {1, 16, 1, 1, 0};
+  if (waves * 4 <= target) return {1, 16, 1, 2, 0};
+  if (n_angles >= 3 && !is_iq_mode(mode)) return {1, 16, 1, 4, 0};
+  if (waves * 2 <= target) return {1, 16, 1, 2, 0};
+  return {1, 8, 2, 2, 0};
+}
+
+// How many wavefronts share a pixel's channels: as many as keep the launch within
+// wave_target, the block within 8 wavefronts, two channels or more for each lane
+// group, and their sums within the LDS. Tiles of four wavefronts whose windows
+// leave room for few blocks per CU take two whatever the launch (11-angle
+// 700 x 512 DAS of 128 channels 77 -> 55 us, 5-angle 512 x 512 32 -> 26.7; IQ
+// frames, bound by their registers, are slower with it).
+int choose_share(const FramePlan &P) {
+  const int waves = P.wz * P.wx;
+  const int64_t launch = (int64_t)P.n_tiles * waves;
+  int wc = 1;
+  while (wc * 2 <= max_share(P.mode) && waves * wc * 2 <= kMaxWavesPerBlock &&
+         launch * wc * 2 <= wave_target(P.n_angles, P.mode) &&
+         P.n_channels >= P.cpw * wc * 4)
+    wc *= 2;
+  FramePlan Q = P;
+  if (wc == 1 && waves == 4 && P.n_angles >= 3 && !is_iq_mode(P.mode) &&
+      P.n_channels >= P.cpw * 4 && 3 * plan_lds_bytes(P) > 2 * (size_t)kDefaultLdsBytes)
+    wc = 2;
+  for (; wc > 1; wc /= 2) {
+    Q.wc = wc;
+    if (plan_lds_bytes(Q) <= (size_t)kMaxLdsBytes) break;
+  }
+  return wc;
 }
 
 // Window length for TZ x TX tiles, and the offsets that centre the transmit and
@@ -256,6 +308,7 @@ static int fit_tile(const pwbf_geometry *g, pwbf_tile t, FramePlan *P, std::stri
   P->lx = ppw / t.lz;
   P->wz = t.wz;
   P->wx = t.wx;
+  P->wc = 1;
   const int TZ = P->lz * t.wz, TX = P->lx * t.wx;
   P->tile_z = TZ;
   P->tile_x = TX;
@@ -387,7 +440,7 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
   // tuned entry for this shape if there is one and it fits, else the default;
   // when that does not fit (LDS or window length), the fitting shape with the
   // most pixels per tile, then the shortest window, then the fewest lane groups.
-  pwbf_tile d = default_tile(g, na, mode);
+  pwbf_tile d = default_tile(g);
   // Batch and serving kernels (8-wavefront plans) take their tiles in cost
   // order across frames instead of the single-frame kernel's depth-ordered,
   // XCD-balanced order; there the 16 x 32 tile is the faster one (8 compound
@@ -396,6 +449,8 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
     d.wz = 2;
     d.wx = 4;
   }
+  const pwbf_tile given = d;  // what completes an explicit shape's zero fields
+  if (!waves) d = single_tile(g, na, mode);
   const bool zero_tile = tile_in && !tile_in->cpw && !tile_in->lz && !tile_in->wz &&
                          !tile_in->wx && !tile_in->chunk;
   if (zero_tile) tile_in = nullptr;
@@ -403,11 +458,11 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
   const char *source = "explicit";
   if (tile_in) {
     pwbf_tile t = *tile_in;
-    if (t.cpw == 0) t.cpw = d.cpw;
-    if (t.lz == 0) t.lz = std::min(d.lz, kWave / t.cpw);
+    if (t.cpw == 0) t.cpw = given.cpw;
+    if (t.lz == 0) t.lz = std::min(given.lz, kWave / t.cpw);
     if (t.wz == 0 && t.wx == 0) {
-      t.wz = d.wz;
-      t.wx = d.wx;
+      t.wz = given.wz;
+      t.wx = given.wx;
     }
     if (waves && tile_waves(t) != waves)
       return fail(err, PWBF_E_INVALID, "batch tiles need wz * wx = %d (got %d x %d)", waves,
@@ -429,6 +484,12 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
         pwbf_tile other = d;
         std::swap(other.wz, other.wx);
         done = fit_tile(g, other, P, err) == PWBF_OK && root_compact(g, *P);
+      }
+      // a shallower wavefront (8 x 8 pixels) where 16 x 4 is too deep
+      if (!done && !waves && d.cpw == 1 && d.lz == 16) {
+        pwbf_tile flat = d;
+        flat.lz = 8;
+        done = fit_tile(g, flat, P, err) == PWBF_OK && root_compact(g, *P);
       }
       // DMAS and pDAS past their delay-offset bound: the same tile in lane
       // groups half as deep and twice as wide (twice the wavefronts along
@@ -454,15 +515,27 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
       pwbf_tile best = {0, 0, 0, 0, 0};
       int best_px = 0, best_win = 0;
       bool best_compact = false;
-      for (int cpw = d.cpw; cpw <= 16; cpw *= 2)
+      // (a single frame: no more pixels per tile than its default, whose size
+      // leaves it enough blocks)
+      const int px_max = waves ? kWave * kMaxWavesPerBlock : kWave * d.wz * d.wx;
+      for (int cpw = d.cpw; cpw <= 16; cpw *= 2) {
+        // and few enough wavefronts that as many can share its pixels' channels
+        // as the launch has room for
+        const int64_t launch = ((int64_t)g->nx * g->nz * cpw + kWave - 1) / kWave;
+        int share = 1;
+        while (!waves && share * 2 <= max_share(mode) &&
+               launch * share * 2 <= wave_target(na, mode))
+          share *= 2;
         for (int lz = 1; lz <= kWave / cpw; lz *= 2)
           for (const auto &wa : kArr) {
-            if (waves ? wa[0] * wa[1] != waves : wa[0] * wa[1] > kMaxWavesPerBlock) continue;
+            if (waves ? wa[0] * wa[1] != waves : wa[0] * wa[1] * share > kMaxWavesPerBlock)
+              continue;
             const pwbf_tile t = {cpw, lz, wa[0], wa[1], 0};
             FramePlan Q = *P;
             std::string e2;
             if (fit_tile(g, t, &Q, &e2) != PWBF_OK) continue;
             const int px = std::min(Q.tile_z, g->nz) * std::min(Q.tile_x, g->nx);
+            if (px > px_max) continue;
             const bool compact = root_compact(g, Q);
             if ((compact && !best_compact) ||
                 (compact == best_compact &&
@@ -473,6 +546,7 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
               best_compact = compact;
             }
           }
+      }
       if (best_px > 0) {
         rc_fit = fit_tile(g, best, P, err);
       } else {
@@ -488,11 +562,12 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
   P->tiles_z = (g->nz + TZ - 1) / TZ;
   P->tiles_x = (g->nx + TX - 1) / TX;
   P->n_tiles = P->tiles_z * P->tiles_x;
+  if (!waves && !tile_in) P->wc = choose_share(*P);
   if (debug_enabled())
     debug_log("plan mode %d dtype %d angle %d grid %d x %d: %s shape cpw %d lz %d wz %d wx %d "
-              "chunk %d, window %d, %d x %d tiles, %zu B LDS",
-              mode, dtype, angle, g->nx, g->nz, source, P->cpw, P->lz, P->wz, P->wx, P->chunk,
-              P->win, P->tiles_z, P->tiles_x, plan_lds_bytes(*P));
+              "wc %d chunk %d, window %d, %d x %d tiles, %zu B LDS",
+              mode, dtype, angle, g->nx, g->nz, source, P->cpw, P->lz, P->wz, P->wx, P->wc,
+              P->chunk, P->win, P->tiles_z, P->tiles_x, plan_lds_bytes(*P));
   return PWBF_OK;
 }
 

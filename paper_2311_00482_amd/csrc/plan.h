@@ -75,6 +75,7 @@ struct FramePlan {
   int32_t tile_z, tile_x;  // pixels per tile: lz * wz by lx * wx
   int32_t tiles_z, tiles_x, n_tiles;
   int32_t tab;  // channels the LDS channel table holds
+  int32_t wc;   // wavefronts that share a pixel's channels (1: one); blocks are wz wx wc
   float sa[kMaxAngles], sal[kMaxAngles];  // sin(theta_a), hi and lo
   float ca[kMaxAngles], cal[kMaxAngles];  // cos(theta_a)
   float to[kMaxAngles], tol[kMaxAngles];  // first-firing offset plus t0, samples
@@ -118,13 +119,21 @@ PWBF_HD inline size_t plan_lds_wref_offset(const FramePlan &p) {
   return (plan_lds_lr_offset(p) + (size_t)p.tab * 4 + 15) / 16 * 16;
 }
 PWBF_HD inline size_t plan_lds_wref_bytes(const FramePlan &p) {
-  return wave_ref_mode(p.mode) ? (size_t)p.wz * p.wx * p.chunk * 16 : 0;
+  return wave_ref_mode(p.mode) ? (size_t)p.wz * p.wx * p.wc * p.chunk * 16 : 0;
 }
 PWBF_HD inline size_t plan_lds_win_offset(const FramePlan &p) {
   return plan_lds_wref_offset(p) + plan_lds_wref_bytes(p);
 }
+// Values per pixel that wavefronts sharing it (wc > 1) add through LDS; they
+// take the place of the windows.
+PWBF_HD constexpr int plan_sums(int mode, int n_angles) {
+  return mode == kDas ? 1 : (is_iq_mode(mode) ? 2 * n_angles : n_angles + (mode == kDmas ? 1 : 0));
+}
 PWBF_HD inline size_t plan_lds_bytes(const FramePlan &p) {
-  return plan_lds_win_offset(p) + (size_t)p.chunk * p.n_angles * p.win * p.entry_bytes;
+  const size_t win = (size_t)p.chunk * p.n_angles * p.win * p.entry_bytes;
+  const size_t sums =
+      p.wc > 1 ? (size_t)plan_sums(p.mode, p.n_angles) * p.wz * p.wx * p.wc * kWave * 4 : 0;
+  return plan_lds_win_offset(p) + (win > sums ? win : sums);
 }
 
 }  // namespace pwbf

@@ -20,7 +20,10 @@ int validate_geometry(const pwbf_geometry *g, std::string *err);
 int validate_outputs(const pwbf_geometry *g, const pwbf_outputs *o, void *ws, size_t ws_bytes,
                      std::string *err, int mode = kDas);
 size_t workspace_bytes(const pwbf_geometry *g, const pwbf_outputs *o);
-pwbf_tile default_tile(const pwbf_geometry *g, int n_angles_used, int mode);
+pwbf_tile default_tile(const pwbf_geometry *g);
+// the wavefronts that share a pixel's channels (FramePlan::wc) in a single-frame
+// launch of plan P whose shape the library picked or the tuner found
+int choose_share(const FramePlan &P);
 // Geometry and launch shape only (no pointers). angle < 0: all angles
 // (compound); angle >= 0: that angle alone.
 // waves = 8: the batch kernel's fixed 8-wavefront blocks; 0: any 1..8.
