@@ -65,19 +65,33 @@ def _as_geom(g, bandpass=False, log_floor_db=-70.0) -> GeometryArg:
     return g if isinstance(g, GeometryArg) else GeometryArg(g, bandpass, log_floor_db)
 
 
-def _stream_ptr(stream, device):
+def _raw_stream(device) -> int:
+    """hipStream_t of torch's current stream on ``device`` (the raw handle, where
+    this torch hands it out: making a Stream object of it takes 2 us, a third of
+    the host time of a small frame's call)."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(int(stream.cuda_stream))
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.type != "cuda" or device.index is None:
+        return int(torch.cuda.current_stream(device).cuda_stream)
+    return raw(device.index)
+
+
+def _stream_ptr(stream, device):
+    return ctypes.c_void_p(_raw_stream(device) if stream is None else int(stream.cuda_stream))
+
+
+_CODES: Dict = {}  # torch dtype -> storage code, by dtype met
 
 
 def _rf_code(rf) -> int:
-    name = str(rf.dtype).replace("torch.", "")
-    if name not in _DTYPES:
-        raise TypeError(f"RF dtype {rf.dtype} not supported (int16, float16, float32, "
-                        "complex64 IQ)")
-    return _DTYPES[name]
+    code = _CODES.get(rf.dtype)
+    if code is None:
+        name = str(rf.dtype).replace("torch.", "")
+        if name not in _DTYPES:
+            raise TypeError(f"RF dtype {rf.dtype} not supported (int16, float16, float32, "
+                            "complex64 IQ)")
+        code = _CODES[rf.dtype] = _DTYPES[name]
+    return code
 
 
 def _ptr(t) -> Optional[int]:
@@ -154,9 +168,10 @@ def _prepare(g, rf, want, out, workspace, bandpass, log_floor_db, p, workspace_n
             out[k] = torch.empty((ga.nx, ga.nz), dtype=torch.float32, device=rf.device)
     o = _abi.Outputs(_ptr(out.get("rf")), _ptr(out.get("filtered")), _ptr(out.get("env")),
                      _ptr(out.get("log")), _ptr(out.get("imag")))
-    need = _abi.lib().pwbf_workspace_bytes(ga.ref, ctypes.byref(o)) if workspace_needed else 0
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=rf.device)
+    if workspace is None and workspace_needed:  # (one given is checked by the call itself)
+        need = _abi.lib().pwbf_workspace_bytes(ga.ref, ctypes.byref(o))
+        if need:
+            workspace = torch.empty(need, dtype=torch.uint8, device=rf.device)
     ws_ptr = _ptr(workspace)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     return ga, o, out, ws_ptr, ws_bytes
@@ -285,13 +300,21 @@ def fk_migrate(g, rf, angle: int = -1, want: Iterable[str] = ("rf", "imag", "env
     return out
 
 
-def _metric_out(torch, n, struct, dev):
-    return torch.empty(n * ctypes.sizeof(struct), dtype=torch.uint8, device=dev)
+def _metric_out(torch, n, struct):
+    """Pinned host memory that the kernel writes: the figures are a few hundred
+    bytes, and reading them there after the wait saves a copy from the device."""
+    return torch.empty(n * ctypes.sizeof(struct), dtype=torch.uint8, pin_memory=True)
 
 
-def _read_structs(buf, struct, n):
-    raw = bytes(buf.cpu().numpy().tobytes())
-    arr = (struct * n).from_buffer_copy(raw)
+def _read_structs(torch, buf, struct, n, stream, device):
+    """The n structs at buf once the stream's work is done."""
+    if stream is None:
+        stream = torch.cuda.current_stream(device)
+    if isinstance(stream, torch.cuda.Stream):
+        stream.synchronize()
+    else:  # another holder of a stream handle
+        torch.cuda.synchronize(device)
+    arr = (struct * n).from_buffer_copy(buf.numpy())
     return [{k: getattr(a, k) for k, _ in struct._fields_} for a in arr]
 
 
@@ -303,11 +326,10 @@ def contrast_metrics(g, env, cysts, stream=None):
     ga = _as_geom(g)
     n = len(cysts)
     arr = (_abi.Cyst * max(1, n))(*[_abi.Cyst(_abi.Disc(*c[0]), _abi.Disc(*c[1])) for c in cysts])
-    out = _metric_out(torch, max(1, n), _abi.Contrast, env.device)
+    out = _metric_out(torch, max(1, n), _abi.Contrast)
     _abi.check(_abi.lib().pwbf_contrast_metrics(ga.ref, _ptr(env), arr, n, _ptr(out),
                                                 _stream_ptr(stream, env.device)))
-    torch.cuda.synchronize(env.device)
-    res = _read_structs(out, _abi.Contrast, n)
+    res = _read_structs(torch, out, _abi.Contrast, n, stream, env.device)
     for r in res:
         r["mu_in"], r["mu_out"] = float(r["mu_in"]), float(r["mu_out"])
     return res
@@ -320,11 +342,10 @@ def resolution_metrics(g, env, targets, stream=None):
     ga = _as_geom(g)
     n = len(targets)
     arr = (_abi.Disc * max(1, n))(*[_abi.Disc(*t) for t in targets])
-    out = _metric_out(torch, max(1, n), _abi.Resolution, env.device)
+    out = _metric_out(torch, max(1, n), _abi.Resolution)
     _abi.check(_abi.lib().pwbf_resolution_metrics(ga.ref, _ptr(env), arr, n, _ptr(out),
                                                   _stream_ptr(stream, env.device)))
-    torch.cuda.synchronize(env.device)
-    return _read_structs(out, _abi.Resolution, n)
+    return _read_structs(torch, out, _abi.Resolution, n, stream, env.device)
 
 
 def beamform_iqdas(g, iq, angle: int, **kw) -> Dict:
