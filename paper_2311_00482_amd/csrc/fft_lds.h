@@ -1,16 +1,22 @@
 #pragma once
-// Block FFT in LDS for gfx950: Stockham autosort passes of radix 16 (the last
-// pass takes the remaining 2, 4 or 8), so a 4096-point transform is three
-// passes with the butterflies' values held in registers, natural order in and
-// out, instead of twelve radix-2 stages.
+// FFTs of several rows of equal length in one 256-thread block for gfx950, sixteen
+// points a thread: the transforms along the array of the f-k migrations, whose 4096
+// points per block are 4 to 1024 rows. Stockham autosort passes of radix 16 (the
+// last takes the remaining 2, 4 or 8), natural order in and out. The first pass
+// takes its points from the caller's load and the last gives them to its store, so
+// that a 256-point row crosses LDS once; the points of a butterfly are those that
+// the load computes or reads side by side over the threads. With the rows written to
+// LDS, transformed there and read back, the transforms of an 11-angle compound of
+// 128 channels and 4096 samples took 21.8 us instead of 16.2 (and its remap and
+// inverse transforms 26.2 instead of 22.6), of one 64-channel record of 2048 samples
+// 7.5 instead of 4.6. (Rows along time: fft_reg.h.)
 //
 // A pass of radix R over n = 2^L points with stride NS (the product of the
 // earlier radices): butterfly j (0 <= j < n / R) reads x[j + r n / R],
 // r < R, multiplies element r by W_{NS R}^{k r} with k = j mod NS, takes an
 // R-point DFT in registers and writes element r to x[(j - k) R + k + r NS].
-// Every butterfly of the pass reads before a barrier and writes after it, so
-// the pass works in place. Several rows (transforms of the same length) can
-// share a block: row q occupies x[q * padded(n) ...].
+// Every butterfly of a pass over LDS reads before a barrier and writes after it, so
+// the pass works in place. Row q occupies x[q * row_stride(n, ROWS) ...].
 //
 // LDS positions are padded by one element every 16 (pad(i) = i + i / 16): the
 // first pass writes with a stride of 16 elements, which would otherwise put all
@@ -21,6 +27,8 @@
 // inverse transform (no 1/n) swaps real and imaginary parts around the
 // forward DFT, which conjugates the twiddles.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "fft_twiddles.h"
 
@@ -159,86 +167,68 @@ __device__ __forceinline__ void powers(int b, float2 (&t)[R]) {
   }
 }
 
-template <int R, int NS, int L, bool INV, int ROWS>
-__device__ __forceinline__ void pass(float2 *x) {
-  constexpr int n = 1 << L, nr = n / R, total = nr * ROWS;
-  constexpr int K = (total + kThreads - 1) / kThreads;  // butterflies per thread
-  static_assert(n <= detail::kTwN, "transforms up to 4096 points");
-  // twiddle W_{NS R}^{k r} = W_4096^{k r tw4096}
+// The transform of ROWS rows of 2^L points whose first pass takes its points from
+// load(row, index) and whose last leaves them in store(row, index, value), so that
+// the rows cross LDS only between passes (once at 128 and 256 points). IN_ROWS
+// (OUT_ROWS): consecutive threads of the first (last) pass take consecutive rows of
+// one index, else consecutive indices of one row. FromLds: the rows are in x.
+struct FromLds {};
+
+template <int L, int DONE, bool INV, int ROWS, bool IN_ROWS, bool OUT_ROWS, class Load, class Store>
+__device__ __forceinline__ void passes_io(float2 *x, const Load &load, const Store &store) {
+  constexpr int RB = (L - DONE) >= 4 ? 4 : (L - DONE), R = 1 << RB, NS = 1 << DONE;
+  constexpr int n = 1 << L, nr = n / R, total = nr * ROWS, K = total / kThreads;
+  static_assert(n <= detail::kTwN && total % kThreads == 0, "whole butterflies for every thread");
   constexpr int stride = row_stride(n, ROWS), tw4096 = detail::kTwN / (NS * R);
+  constexpr bool first = DONE == 0, last = DONE + RB == L;
+  constexpr bool in_lds = !first || std::is_same_v<Load, FromLds>;
+  constexpr bool by_rows = first ? IN_ROWS : (last && OUT_ROWS);
   float2 v[K][R];
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const int t = (int)threadIdx.x + q * kThreads;
-    if (total % kThreads == 0 || t < total) {
-      const int row = t / nr, j = t % nr, k = j & (NS - 1);
-      const float2 *xr = x + row * stride;
+    const int row = by_rows ? t % ROWS : t / nr, j = by_rows ? t / ROWS : t % nr;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float2 a = xr[pad(j + r * nr)];
-        v[q][r] = INV ? swap(a) : a;
-      }
-      if constexpr (NS > 1) {
-        float2 t[R];
-        powers<R>(k * tw4096, t);
-#pragma unroll
-        for (int r = 1; r < R; ++r)
-          // inverse: swap(z conj(w)) = swap(z) w, so the swapped values take w itself
-          v[q][r] = cmul(v[q][r], t[r]);
-      }
-      dft<R>(v[q]);
+    for (int r = 0; r < R; ++r) {
+      float2 a;
+      if constexpr (in_lds)
+        a = x[row * stride + pad(j + r * nr)];
+      else
+        a = load(row, j + r * nr);
+      v[q][r] = INV ? swap(a) : a;
     }
+    if constexpr (!first) {
+      float2 w[R];
+      powers<R>((j & (NS - 1)) * tw4096, w);
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[q][r] = cmul(v[q][r], w[r]);
+    }
+    dft<R>(v[q]);
   }
-  __syncthreads();
+  if constexpr (in_lds && !last) __syncthreads();  // in place
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const int t = (int)threadIdx.x + q * kThreads;
-    if (total % kThreads == 0 || t < total) {
-      const int row = t / nr, j = t % nr, k = j & (NS - 1);
-      float2 *xr = x + row * stride;
-      const int o = (j - k) * R + k;
+    const int row = by_rows ? t % ROWS : t / nr, j = by_rows ? t / ROWS : t % nr;
+    const int k = j & (NS - 1), o = (j - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) xr[pad(o + r * NS)] = INV ? swap(v[q][r]) : v[q][r];
+    for (int r = 0; r < R; ++r) {
+      const float2 b = INV ? swap(v[q][r]) : v[q][r];
+      if constexpr (last)
+        store(row, o + r * NS, b);
+      else
+        x[row * stride + pad(o + r * NS)] = b;
     }
   }
-  __syncthreads();
-}
-
-template <int L, int DONE, bool INV, int ROWS>
-__device__ __forceinline__ void passes(float2 *x) {
-  if constexpr (DONE < L) {
-    constexpr int RB = (L - DONE) >= 4 ? 4 : (L - DONE);
-    pass<1 << RB, 1 << DONE, L, INV, ROWS>(x);
-    passes<L, DONE + RB, INV, ROWS>(x);
+  if constexpr (!last) {
+    __syncthreads();
+    passes_io<L, DONE + RB, INV, ROWS, IN_ROWS, OUT_ROWS>(x, load, store);
   }
 }
 
-// In-place transform of ROWS rows of 2^L points at x (padded layout, rows
-// row_stride(2^L, ROWS) apart). Starts
-// and ends with a barrier-consistent LDS state: callers write x and
-// __syncthreads() before, read after.
-template <int L, bool INV, int ROWS = 1>
-__device__ __forceinline__ void transform(float2 *x) {
-  passes<L, 0, INV, ROWS>(x);
-}
-
-// One row, L known only at run time (uniform over the block), 1 <= L <= 12.
-template <bool INV>
-__device__ __forceinline__ void transform_any(float2 *x, int L) {
-  switch (L) {
-    case 1: transform<1, INV>(x); break;
-    case 2: transform<2, INV>(x); break;
-    case 3: transform<3, INV>(x); break;
-    case 4: transform<4, INV>(x); break;
-    case 5: transform<5, INV>(x); break;
-    case 6: transform<6, INV>(x); break;
-    case 7: transform<7, INV>(x); break;
-    case 8: transform<8, INV>(x); break;
-    case 9: transform<9, INV>(x); break;
-    case 10: transform<10, INV>(x); break;
-    case 11: transform<11, INV>(x); break;
-    default: transform<12, INV>(x); break;
-  }
+template <int L, bool INV, int ROWS, bool IN_ROWS, bool OUT_ROWS, class Load, class Store>
+__device__ __forceinline__ void transform_io(float2 *x, const Load &load, const Store &store) {
+  passes_io<L, 0, INV, ROWS, IN_ROWS, OUT_ROWS>(x, load, store);
 }
 
 }  // namespace fft

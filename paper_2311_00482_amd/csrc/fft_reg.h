@@ -1,15 +1,16 @@
 #pragma once
 // FFTs whose points stay in registers between passes, for rows that are loaded,
 // transformed, weighted, transformed back and stored by the same threads: the
-// depth post-processing and the IQ demodulation.
+// depth post-processing, the IQ demodulation and the f-k migrations' transforms along
+// time.
 //
 // A row of n = 2^L points belongs to T = n / 8 threads with E = 8 points each: a
 // row of up to 512 points is one wavefront or a part of one, so its passes need
-// no barrier, and every thread has a butterfly in every pass. (The in-LDS engine
-// of fft_lds.h gives one 256-thread block to a row; at 512 points its radix-16
-// passes keep 32 of the threads busy. Sixteen points a thread from 1024 points on
-// were slower: 128 registers and, at 4096, spills.) Passes are Stockham's as there: radix E, the last pass (the
-// first of the inverse) takes the remaining factor. Point (q, r) of thread t,
+// no barrier, and every thread has a butterfly in every pass. (With one 256-thread
+// block to a row in LDS, radix-16 passes over 512 points kept 32 of the threads
+// busy. Sixteen points a thread from 1024 points on were slower: 128 registers and,
+// at 4096, spills.) Passes are Stockham's as in fft_lds.h: radix E, the last pass
+// (the first of the inverse) takes the remaining factor. Point (q, r) of thread t,
 // butterfly q of E / R, is x[t + q T + r n / R]: the first pass loads it from
 // memory and the last leaves it at the same index, so a row crosses LDS only
 // between passes (twice per 512-point transform), and a spectrum is weighted in
@@ -83,7 +84,8 @@ __host__ __device__ constexpr bool palindromic(int L) {
   return radix_bits(L, 0) == radix_bits(L, passes(L) - 1);
 }
 
-// Twiddle bases of the passes after the first of one direction: w, w^2, w^4 of W_{NS R}^k, per butterfly whose k differs.
+// Twiddle bases of the passes after the first of one direction: w, w^2, w^4 of
+// W_{NS R}^k, per butterfly whose k differs.
 template <int L, bool INV, int I = 1>
 struct Twiddles {
   static constexpr int RB = radix_bits(L, I, INV), R = 1 << RB, NSB = done_bits(L, I, INV);

@@ -8,7 +8,7 @@
 
 namespace pwbf {
 
-constexpr int kFkMaxSamples = 4096;  // one LDS FFT along time per block
+constexpr int kFkMaxSamples = 4096;  // one FFT along time
 constexpr int kFkMaxNx = 1024;       // zero-padded array length (2 or 4 x channels)
 constexpr int kFkRowPoints = 4096;   // points per block of the kx transforms (rows x Nx)
 

@@ -1,11 +1,17 @@
 // f-k migrations (Stolt's and Lu's) for steered plane waves. Every stage runs
 // over all angles of the call in one launch (blockIdx.y selects the angle), so
 // even a single frame gives the chip thousands of blocks. The two methods share
-// every stage but the remap. Transforms run in LDS (fft_lds.h); the two
-// transposes between channel-major and bin-major data happen in LDS, inside
-// blocks that hold several rows, so every global access is a contiguous run:
+// every stage but the remap. Transforms keep their points in registers between
+// passes, and the two transposes between channel-major and bin-major data happen
+// inside blocks that hold several rows, so every global access is a contiguous run.
+// Bound by instruction issue (transforms, float-float positions) and by the planes
+// between the stages (230 MB for 11 angles of 128 channels and 4096 samples, which
+// the 256 MB cache holds in part). That compound, 1024 x 1024 pixels: time 15.4 us,
+// space 16.2, remap 22.6, itime 17.7, image 24 (with every transform
+// in LDS by 256 threads: 16.6, 21.8, 26.2, 21.0); one 64-channel record of
+// 2048 samples on 500 x 512: 5.2, 4.6, 11.6, 4.0, 4.1 (6.8, 7.5, 12.1, 5.9, 4.2).
 //
-//  k_fk_time      block per (channel pair, angle): one complex FFT of two traces
+//  k_fk_time      row per (channel pair, angle): one complex FFT of two traces
 //                 (Nt samples each, as real and imaginary parts), split into the
 //                 two spectra; the positive bins times exp(2 pi i k c_e) (the trace
 //                 advanced by its element's firing delay and shifted to t = 0) go
@@ -25,7 +31,7 @@
 //                   receive wavenumber j - u cos / 2 is negative -
 //                 then inverse FFTs along kx, and writes the window's columns
 //                 transposed, U[e][j0..j0+ROWS)
-//  k_fk_itime     block per window column x1 (and angle): inverse FFT along kz of
+//  k_fk_itime     row per window column x1 (and angle): inverse FFT along kz of
 //                 U[e][.], zero-filled to Nt, scaled by 1/(Nx Nt); stores the
 //                 window's rows of M
 //  k_fk_image     thread per two pixels (adjacent columns, one depth): for every
@@ -42,6 +48,7 @@
 #include <hip/hip_runtime.h>
 
 #include "beamform_device.h"
+#include "fft_reg.h"
 #include "fk.h"
 #include "postz_device.h"
 
@@ -52,7 +59,7 @@ namespace {
 using dev::ff;
 using fft::cmul;
 
-constexpr int kFkThreads = fft::kThreads;  // every block runs the in-LDS transforms
+constexpr int kFkThreads = fft::kThreads;  // of the blocks along the array
 
 template <int DT>
 __device__ __forceinline__ float trace_sample(const void *rf, size_t i) {
@@ -83,50 +90,78 @@ __device__ __forceinline__ int split_index(ff u, float *frac) {
 
 __device__ __forceinline__ int kbins_of(const FkPlan &F) { return (1 << F.log2nt) / 2 + 1; }
 
-// Two traces per block: channels e0 = 2 blockIdx.x and e0 + 1 go in as the
-// real and imaginary parts of one complex sequence z (a missing second trace
-// is zero). With Z its DFT and Z(Nt) = Z(0), the traces' spectra are
-// X0(k) = (Z(k) + conj Z(Nt - k)) / 2 and X1(k) = (Z(k) - conj Z(Nt - k)) / (2i).
-template <int DT>
-__global__ void __launch_bounds__(kFkThreads) k_fk_time(FkPlan F) {
+// The transforms along time run in registers, eight points a thread (fft_reg.h): a
+// block holds kTimeRows<L> rows of 2^L points, one from 512 points on.
+template <int L>
+constexpr int kTimeThreads = fftr::threads(L) < kWave ? kWave : fftr::threads(L);
+template <int L>
+constexpr int kTimeRows = kTimeThreads<L> / fftr::threads(L);
+template <int L>
+constexpr size_t kTimeLds = (size_t)fftr::padded<L>() * kTimeRows<L> * 8;
+
+// Two traces per row: channels e0 and e0 + 1 go in as the real and imaginary parts
+// of one complex sequence z (a missing second trace is zero). With Z its DFT and
+// Z(Nt) = Z(0), the traces' spectra are X0(k) = (Z(k) + conj Z(Nt - k)) / 2 and
+// X1(k) = (Z(k) - conj Z(Nt - k)) / (2i).
+template <int L, int DT>
+__global__ void __launch_bounds__(kTimeThreads<L>) k_fk_time(FkPlan F) {
   extern __shared__ __align__(16) float2 sm[];
-  const int nt = 1 << F.log2nt, kbins = kbins_of(F), e0 = 2 * blockIdx.x, a = blockIdx.y;
-  const bool two = e0 + 1 < F.n_ch;
+  constexpr int nt = 1 << L, kbins = nt / 2 + 1, T = fftr::threads(L), E = fftr::points(L);
+  const int row = threadIdx.x / T, t = threadIdx.x % T, a = blockIdx.y;
+  const int e0 = 2 * (blockIdx.x * kTimeRows<L> + row);
+  const bool one = e0 < F.n_ch, two = e0 + 1 < F.n_ch;
   // the frame maximum that the image kernel, last of the call, folds into
   if (F.ws_max && blockIdx.x == 0 && blockIdx.y == 0) dev::frame_max_clear(F.ws_max, threadIdx.x);
-  float2 *x = sm;
-  const size_t base = ((size_t)a * F.n_ch + e0) * nt;
-  const size_t base1 = two ? base + nt : base;  // every read inside the record array
-  for (int k = threadIdx.x; k < nt; k += kFkThreads) {
+  float2 *x = sm + row * fftr::padded<L>();
+  // every read inside the record array
+  const size_t base = ((size_t)a * F.n_ch + (one ? e0 : 0)) * nt;
+  const size_t base1 = two ? base + nt : base;
+  float2 v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int k = fftr::index_of<L, false>(e, t);
     const float v1 = trace_sample<DT>(F.rf, base1 + k);
-    x[fft::pad(k)] = make_float2(trace_sample<DT>(F.rf, base + k), two ? v1 : 0.f);
+    v[e] = make_float2(trace_sample<DT>(F.rf, base + k), two ? v1 : 0.f);
   }
-  __syncthreads();
-  fft::transform_any<false>(x, F.log2nt);
+  fftr::TwiddlesOf<L, false> tw;
+  tw.load(t);
+  fftr::transform<L, false>(v, tw, x, t);
+  fftr::row_sync<L>();  // the last exchange's reads are done
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int k = fftr::index_of<L, true>(e, t);
+    if (k == 0 || k >= nt / 2) x[fftr::pad<L>(k)] = v[e];
+  }
+  fftr::row_sync<L>();
   const FkAngleConst &A = F.ang[a];
   const ff c0 = dev::ff_add({A.c0_hi, A.c0_lo}, dev::ff_mul(ffi(e0), {A.c1_hi, A.c1_lo}));
   const ff c1 = dev::ff_add({A.c0_hi, A.c0_lo}, dev::ff_mul(ffi(e0 + 1), {A.c1_hi, A.c1_lo}));
   // T[a][k / R][e][k mod R]: the pair's rows of a block are adjacent, 2 R bins
   const int LR = 12 - F.log2nx, R = 1 << LR;
-  float2 *T0 = F.T + (size_t)a * F.n_ch * fk_kbins_padded(F.log2nt, F.log2nx) + e0 * R;
-  // exp(2 pi i k c) at the thread's first bin, then by the step of kFkThreads
-  // bins: a thread's bins are at most 9 products from an accurate phase
+  float2 *T0 = F.T + (size_t)a * F.n_ch * fk_kbins_padded(L, F.log2nx) + e0 * R;
+  // exp(2 pi i k c) at the thread's first bin, then by the step of T bins: a thread's
+  // bins t + m T are at most five products from an accurate phase
   float sn, cs;
-  sincospif(2.0f * frac_revs(threadIdx.x, c0), &sn, &cs);
+  sincospif(2.0f * frac_revs(t, c0), &sn, &cs);
   float2 ph0 = make_float2(cs, sn);
-  sincospif(2.0f * frac_revs(kFkThreads, c0), &sn, &cs);
+  sincospif(2.0f * frac_revs(T, c0), &sn, &cs);
   const float2 step0 = make_float2(cs, sn);
-  sincospif(2.0f * frac_revs(threadIdx.x, c1), &sn, &cs);
+  sincospif(2.0f * frac_revs(t, c1), &sn, &cs);
   float2 ph1 = make_float2(cs, sn);
-  sincospif(2.0f * frac_revs(kFkThreads, c1), &sn, &cs);
+  sincospif(2.0f * frac_revs(T, c1), &sn, &cs);
   const float2 step1 = make_float2(cs, sn);
-  for (int k = threadIdx.x; k < kbins; k += kFkThreads) {
-    const float2 z = x[fft::pad(k)], w = x[fft::pad((nt - k) & (nt - 1))];  // Z(k), Z(Nt - k)
-    const float2 x0 = make_float2(0.5f * (z.x + w.x), 0.5f * (z.y - w.y));
-    const float2 x1 = make_float2(0.5f * (z.y + w.y), 0.5f * (w.x - z.x));
-    float2 *t = T0 + (size_t)(k >> LR) * F.n_ch * R + (k & (R - 1));
-    t[0] = cmul(x0, ph0);
-    if (two) t[R] = cmul(x1, ph1);
+  constexpr int RL = 1 << fftr::radix_bits(L, fftr::passes(L) - 1), Q = E / RL;
+#pragma unroll
+  for (int m = 0; m <= E / 2; ++m) {
+    const int k = t + m * T, e = m % Q * RL + m / Q;  // v[e] is bin k
+    if (k < kbins && one) {
+      const float2 z = v[e], w = x[fftr::pad<L>((nt - k) & (nt - 1))];  // Z(k), Z(Nt - k)
+      const float2 x0 = make_float2(0.5f * (z.x + w.x), 0.5f * (z.y - w.y));
+      const float2 x1 = make_float2(0.5f * (z.y + w.y), 0.5f * (w.x - z.x));
+      float2 *q = T0 + (size_t)(k >> LR) * F.n_ch * R + (k & (R - 1));
+      q[0] = cmul(x0, ph0);
+      if (two) q[R] = cmul(x1, ph1);
+    }
     ph0 = cmul(ph0, step0);
     ph1 = cmul(ph1, step1);
   }
@@ -134,33 +169,23 @@ __global__ void __launch_bounds__(kFkThreads) k_fk_time(FkPlan F) {
 
 template <int L, int METHOD>
 __global__ void __launch_bounds__(kFkThreads) k_fk_space(FkPlan F) {
-  constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L, stride = fft::row_stride(nx, ROWS);
+  constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L;
   extern __shared__ __align__(16) float2 sm[];
-  float2 *x = sm;
   const int kbins = kbins_of(F), k0 = blockIdx.x * ROWS, a = blockIdx.y;
   // the block's bins of every channel are one contiguous run of T (bins past
   // the last are never written and read as zero)
   const float2 *T = F.T + ((size_t)a * fk_kbins_padded(F.log2nt, L) + k0) * F.n_ch;
-  for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
-    const int e = t / ROWS, r = t - e * ROWS, k = k0 + r;
-    x[r * stride + fft::pad(e)] = (e < F.n_ch && k < kbins) ? T[t] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  fft::transform<L, false, ROWS>(x);
   float2 *P = F.P + (size_t)a * kbins * nx;
-  if (METHOD == kFkStolt) {
-    // Stolt's remap reads along frequency at fixed kx: store P[m][k], consecutive
-    // threads on consecutive bins
-    for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
-      const int m = t / ROWS, r = t - m * ROWS, k = k0 + r;
-      if (k < kbins) P[(size_t)m * kbins + k] = x[r * stride + fft::pad(m)];
-    }
-  } else {
-    for (int t = threadIdx.x; t < nx * ROWS; t += kFkThreads) {
-      const int r = t >> L, m = t & (nx - 1), k = k0 + r;
-      if (k < kbins) P[(size_t)k * nx + m] = x[r * stride + fft::pad(m)];
-    }
-  }
+  auto load = [&](int r, int e) {
+    return e < F.n_ch && k0 + r < kbins ? T[e * ROWS + r] : make_float2(0.f, 0.f);
+  };
+  // Stolt's remap reads along frequency at fixed kx: store P[m][k], consecutive
+  // threads on consecutive bins
+  auto store = [&](int r, int m, float2 v) {
+    const unsigned k = k0 + r;
+    if ((int)k < kbins) P[METHOD == kFkStolt ? m * kbins + k : k * nx + m] = v;
+  };
+  fft::transform_io<L, false, ROWS, true, METHOD == kFkStolt>(sm, load, store);
 }
 
 // Float-float helpers with hardware reciprocal and square root in the leading
@@ -213,38 +238,33 @@ struct RemapCells {
   __device__ static int r0() { return nx >= kFkThreads ? 0 : (int)threadIdx.x >> L; }
 };
 
-// Stolt's remap of the block's rows: the cell (j, m) takes the data spectrum at
-// bin u = sqrt((alpha m')^2 + j^2), linearly (zeros past the last bin), times
-// j / u. P is stored [m][k]; consecutive threads take consecutive rows j of one
-// column, so their bins u are close and the gathers contiguous.
+// Stolt's remap: the cell (j, m) takes the data spectrum at bin
+// u = sqrt((alpha m')^2 + j^2), linearly (zeros past the last bin), times j / u.
+// P is stored [m][k]; consecutive threads take consecutive rows j of one column, so
+// their bins u are close and the gathers contiguous.
 template <int L>
-__device__ __forceinline__ void stolt_rows(const FkAngleConst &A, const float2 *__restrict__ P,
-                                           int j0, int kbins, float2 *x) {
-  constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L, LR = 12 - L;
-  constexpr int stride = fft::row_stride(nx, ROWS);
-  static_assert((1 << LR) == ROWS, "rows of a block");
-#pragma unroll 4
-  for (int t = threadIdx.x; t < kFkRowPoints; t += kFkThreads) {
-    const int r = t & (ROWS - 1), m = t >> LR, ms = m < nx / 2 ? m : m - nx;
-    const int j = min(j0 + r, kbins - 1);  // rows past the last bin store zero below
-    const float fj = (float)j;
-    const ff am = dev::ff_mul(ffi(ms), {A.m0_hi, A.m0_lo});
-    const ff am2 = dev::ff_mul(am, am);  // (alpha m')^2
-    const ff u2 = dev::two_sum(am2.hi, fj * fj);  // j^2 < 2^24 is exact
-    const ff u2n = dev::two_sum(u2.hi, u2.lo + am2.lo);
-    const bool in_band = u2n.hi > 0.f && u2n.hi < (float)(kbins + 1) * (float)(kbins + 1);
-    const ff u = ff_sqrt_hw(in_band ? u2n : ff{1.f, 0.f});
-    float w;
-    const int i0 = split_index(u, &w);
-    // clamped loads, always issued; taps outside the spectrum weigh zero
-    const bool ok = in_band && i0 >= 0 && i0 <= kbins - 1 && j0 + r < kbins;
-    const int ia = ok ? i0 : 0, ib = min(ia + 1, kbins - 1);
-    const unsigned cb = (unsigned)(m * kbins);  // < 2^21 cells per angle
-    const float2 lo = P[cb + ia], hi = P[cb + ib];
-    const float jac = ok ? fj * __builtin_amdgcn_rcpf(u.hi) : 0.f;
-    const float wl = (1.f - w) * jac, wh = (ok && i0 + 1 <= kbins - 1) ? w * jac : 0.f;
-    x[r * stride + fft::pad(m)] = make_float2(wl * lo.x + wh * hi.x, wl * lo.y + wh * hi.y);
-  }
+__device__ __forceinline__ float2 stolt_cell(const FkAngleConst &A, const float2 *__restrict__ P,
+                                             int j0, int r, int m, int kbins) {
+  constexpr int nx = 1 << L;
+  const int ms = m < nx / 2 ? m : m - nx;
+  const int j = min(j0 + r, kbins - 1);  // rows past the last bin are zero below
+  const float fj = (float)j;
+  const ff am = dev::ff_mul(ffi(ms), {A.m0_hi, A.m0_lo});
+  const ff am2 = dev::ff_mul(am, am);  // (alpha m')^2
+  const ff u2 = dev::two_sum(am2.hi, fj * fj);  // j^2 < 2^24 is exact
+  const ff u2n = dev::two_sum(u2.hi, u2.lo + am2.lo);
+  const bool in_band = u2n.hi > 0.f && u2n.hi < (float)(kbins + 1) * (float)(kbins + 1);
+  const ff u = ff_sqrt_hw(in_band ? u2n : ff{1.f, 0.f});
+  float w;
+  const int i0 = split_index(u, &w);
+  // clamped loads, always issued; taps outside the spectrum weigh zero
+  const bool ok = in_band && i0 >= 0 && i0 <= kbins - 1 && j0 + r < kbins;
+  const int ia = ok ? i0 : 0, ib = min(ia + 1, kbins - 1);
+  const unsigned cb = (unsigned)(m * kbins);  // < 2^21 cells per angle
+  const float2 lo = P[cb + ia], hi = P[cb + ib];
+  const float jac = ok ? fj * __builtin_amdgcn_rcpf(u.hi) : 0.f;
+  const float wl = (1.f - w) * jac, wh = (ok && i0 + 1 <= kbins - 1) ? w * jac : 0.f;
+  return make_float2(wl * lo.x + wh * hi.x, wl * lo.y + wh * hi.y);
 }
 
 // Lu's remap of the block's rows: the cell (j, m) takes the data spectrum at
@@ -302,44 +322,56 @@ __device__ __forceinline__ void lu_rows(const FkAngleConst &A, const float2 *__r
 
 template <int L, int METHOD>
 __global__ void __launch_bounds__(kFkThreads) k_fk_remap(FkPlan F) {
-  constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L, stride = fft::row_stride(nx, ROWS);
+  constexpr int nx = 1 << L, ROWS = kFkRowPoints >> L;
   extern __shared__ __align__(16) float2 sm[];
-  float2 *x = sm;
   const int kbins = kbins_of(F), j0 = blockIdx.x * ROWS, a = blockIdx.y;
   const FkAngleConst &A = F.ang[a];
   const float2 *P = F.P + (size_t)a * kbins * nx;
-  if (METHOD == kFkLu)
-    lu_rows<L>(A, P, j0, kbins, x);
-  else
-    stolt_rows<L>(A, P, j0, kbins, x);
-  __syncthreads();
-  fft::transform<L, true, ROWS>(x);
   // the window's columns, transposed: consecutive threads take consecutive rows
   float2 *U = F.U + (size_t)a * nx * kbins;
-  for (int t = threadIdx.x; t < A.ncol * ROWS; t += kFkThreads) {
-    const int c = t / ROWS, r = t - c * ROWS, j = j0 + r, e = A.col0 + c;
-    if (j < kbins) U[(size_t)e * kbins + j] = x[r * stride + fft::pad(e)];
+  auto store = [&](int r, int e, float2 v) {
+    if ((unsigned)(e - A.col0) < (unsigned)A.ncol && j0 + r < kbins)
+      U[(unsigned)(e * kbins + j0 + r)] = v;
+  };
+  if constexpr (METHOD == kFkLu) {
+    lu_rows<L>(A, P, j0, kbins, sm);
+    __syncthreads();
+    fft::transform_io<L, true, ROWS, false, true>(sm, fft::FromLds(), store);
+  } else {
+    auto load = [&](int r, int m) { return stolt_cell<L>(A, P, j0, r, m, kbins); };
+    fft::transform_io<L, true, ROWS, true, true>(sm, load, store);
   }
 }
 
-__global__ void __launch_bounds__(kFkThreads) k_fk_itime(FkPlan F) {
+template <int L>
+__global__ void __launch_bounds__(kTimeThreads<L>) k_fk_itime(FkPlan F) {
   extern __shared__ __align__(16) float2 sm[];
-  const int a = blockIdx.y;
+  constexpr int nt = 1 << L, kbins = nt / 2 + 1, T = fftr::threads(L), E = fftr::points(L);
+  const int row = threadIdx.x / T, t = threadIdx.x % T, a = blockIdx.y, nx = 1 << F.log2nx;
   const FkAngleConst &A = F.ang[a];
-  if ((int)blockIdx.x >= A.ncol) return;  // the whole block: outside this angle's window
-  const int nt = 1 << F.log2nt, nx = 1 << F.log2nx, kbins = kbins_of(F);
-  const int col = A.col0 + blockIdx.x;
-  float2 *x = sm;
+  const int c = blockIdx.x * kTimeRows<L> + row;
+  if ((int)blockIdx.x * kTimeRows<L> >= A.ncol) return;  // the whole block: outside the window
+  const bool mine = c < A.ncol;
+  const int col = A.col0 + (mine ? c : 0);
   const float2 *I = F.U + ((size_t)a * nx + col) * kbins;
-  for (int j = threadIdx.x; j < nt; j += kFkThreads)
-    x[fft::pad(j)] = j < kbins ? I[j] : make_float2(0.f, 0.f);
-  __syncthreads();
-  fft::transform_any<true>(x, F.log2nt);
+  float2 v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int j = fftr::index_of<L, false>(e, t);
+    v[e] = j < kbins ? I[j] : make_float2(0.f, 0.f);
+  }
+  fftr::TwiddlesOf<L, false> tw;  // a forward transform with the parts swapped
+  tw.load(t);
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = fft::swap(v[e]);
+  fftr::transform<L, false>(v, tw, sm + row * fftr::padded<L>(), t);
   const float scale = 1.0f / ((float)nx * (float)nt);
   float2 *out = F.M + ((size_t)a * nx + col) * nt;
-  for (int l = A.row0 + threadIdx.x; l < A.row0 + A.nrow; l += kFkThreads) {
-    const float2 v = x[fft::pad(l)];
-    out[l] = make_float2(v.x * scale, v.y * scale);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int l = fftr::index_of<L, true>(e, t);
+    if (mine && (unsigned)(l - A.row0) < (unsigned)A.nrow)
+      out[l] = make_float2(v[e].y * scale, v[e].x * scale);
   }
 }
 
@@ -480,21 +512,45 @@ hipError_t launch_rows(const FkPlan &F, hipStream_t s) {
   return hipGetLastError();
 }
 
+// the transform along time of the records (ncol < 0) or of ncol window columns
+template <int L>
+hipError_t launch_time_rows(const FkPlan &F, int ncol, hipStream_t s) {
+  const int rows = ncol < 0 ? (F.n_ch + 1) / 2 : ncol;  // two traces to a row
+  const dim3 grid((rows + kTimeRows<L> - 1) / kTimeRows<L>, F.n_ang), blk(kTimeThreads<L>);
+  if (ncol >= 0)
+    hipLaunchKernelGGL(k_fk_itime<L>, grid, blk, kTimeLds<L>, s, F);
+  else if (F.dtype == kI16)
+    hipLaunchKernelGGL((k_fk_time<L, kI16>), grid, blk, kTimeLds<L>, s, F);
+  else if (F.dtype == kF16)
+    hipLaunchKernelGGL((k_fk_time<L, kF16>), grid, blk, kTimeLds<L>, s, F);
+  else
+    hipLaunchKernelGGL((k_fk_time<L, kF32>), grid, blk, kTimeLds<L>, s, F);
+  return hipGetLastError();
+}
+
+hipError_t launch_time(const FkPlan &F, int ncol, hipStream_t s) {
+  switch (F.log2nt) {
+    case 1: return launch_time_rows<1>(F, ncol, s);
+    case 2: return launch_time_rows<2>(F, ncol, s);
+    case 3: return launch_time_rows<3>(F, ncol, s);
+    case 4: return launch_time_rows<4>(F, ncol, s);
+    case 5: return launch_time_rows<5>(F, ncol, s);
+    case 6: return launch_time_rows<6>(F, ncol, s);
+    case 7: return launch_time_rows<7>(F, ncol, s);
+    case 8: return launch_time_rows<8>(F, ncol, s);
+    case 9: return launch_time_rows<9>(F, ncol, s);
+    case 10: return launch_time_rows<10>(F, ncol, s);
+    case 11: return launch_time_rows<11>(F, ncol, s);
+    case 12: return launch_time_rows<12>(F, ncol, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_fk(const FkPlan &F, int ncol_max, hipStream_t s) {
-  const int nt = 1 << F.log2nt;
-  const size_t lds_t = fft::lds_bytes(nt, 1);
-  const dim3 blk(kFkThreads);
-  hipError_t e;
-  const dim3 pairs((F.n_ch + 1) / 2, F.n_ang);  // two traces per block
-  if (F.dtype == kI16)
-    hipLaunchKernelGGL(k_fk_time<kI16>, pairs, blk, lds_t, s, F);
-  else if (F.dtype == kF16)
-    hipLaunchKernelGGL(k_fk_time<kF16>, pairs, blk, lds_t, s, F);
-  else
-    hipLaunchKernelGGL(k_fk_time<kF32>, pairs, blk, lds_t, s, F);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipError_t e = launch_time(F, -1, s);
+  if (e != hipSuccess) return e;
   switch (F.log2nx) {
     case 2: e = launch_rows<2>(F, s); break;
     case 3: e = launch_rows<3>(F, s); break;
@@ -509,8 +565,7 @@ hipError_t launch_fk(const FkPlan &F, int ncol_max, hipStream_t s) {
   }
   if (e != hipSuccess) return e;
   if (ncol_max > 0) {
-    hipLaunchKernelGGL(k_fk_itime, dim3(ncol_max, F.n_ang), blk, lds_t, s, F);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_time(F, ncol_max, s)) != hipSuccess) return e;
   }
   const int zchunks = (F.nz_img + 255) / 256;
   hipLaunchKernelGGL(k_fk_image, dim3((F.nx_img + 1) / 2 * zchunks), dim3(256), 0, s, F,
