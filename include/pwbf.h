@@ -405,7 +405,7 @@ typedef struct pwbf_plan_info {
   int32_t win;                /* LDS entries per (channel, angle) window */
   int32_t off_t, off_r;       /* window-delay centring offsets (entries) */
   int32_t tiles_z, tiles_x;   /* tile grid */
-  int32_t threads_per_block;
+  int32_t threads_per_block;  /* 64 wz wx, times the wavefronts that share a pixel */
   int32_t blocks;             /* blocks launched (a multiple of 8) */
   int32_t n_angles_used;      /* angles the kernel sums (1 for single-angle calls) */
   int64_t lds_bytes;          /* LDS per block */
