@@ -88,11 +88,14 @@ __global__ void __launch_bounds__(post_block(L)) __attribute__((amdgpu_waves_per
 // the bins k_lo..k_hi are kept (those within fs / (2 D) of f0, decided on the
 // host), then mixed down, and every D-th sample is kept. The band limit takes the
 // real part off the record itself, so the two-records-per-transform form above
-// does not apply here. The kept bins are fewer than n / D apart, so they fall on
-// different bins of the n / D-point spectrum of the kept samples (bin k mod n / D):
-// the inverse transform has n / D points (448 records of 2048 samples at D = 2:
-// 10.5 -> 8.5 us). Its row needs only a part of the threads
-// of the record's (T / T2 copies of them compute the same, each on LDS of its own).
+// does not apply here. Bin k of the record is bin k mod n / D of the kept samples,
+// so the inverse transform has n / D points (448 records of 2048 samples at D = 2:
+// 10.5 -> 8.5 us). The kept band is n / D bins wide without its edges, but where
+// both edges fall on bins the host's rounded comparison may keep them both
+// (fs = 62.5 MHz / 3, f0 = 5 fs / 16, D = 4: n / D + 1 bins): the upper one,
+// n / D past the lower, is added to the same bin once that is stored. The inverse's row
+// needs only a part of the threads of the record's (T / T2 copies of them compute
+// the same, each on LDS of its own).
 template <int DT, int L, int LD>
 __global__ void __launch_bounds__(post_block(L))
     k_iq_demod_decim(const void *__restrict__ rf, float2 *__restrict__ iq, int rows, int k_lo,
@@ -123,9 +126,18 @@ __global__ void __launch_bounds__(post_block(L))
   for (int e = 0; e < E; ++e) {
     const int k = index_of<L, true>(e, t);
     const float h = dev::analytic_weight(k, n) * (1.0f / n);
-    if (k >= k_lo && k <= k_hi) x[k & (n2 - 1)] = make_float2(v[e].x * h, v[e].y * h);
+    v[e] = make_float2(v[e].x * h, v[e].y * h);
+    if (k >= k_lo && k <= k_hi && k - k_lo < n2) x[k & (n2 - 1)] = v[e];
   }
   row_sync<L>();
+  if (k_hi - k_lo >= n2) {  // the band's upper edge as well as its lower (uniform)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int k = index_of<L, true>(e, t);
+      if (k <= k_hi && k - k_lo >= n2) x[k & (n2 - 1)] = fft::cadd(x[k & (n2 - 1)], v[e]);
+    }
+    row_sync<L>();
+  }
   const int t2 = t & (T2 - 1);
   float2 y[E2];
 #pragma unroll
