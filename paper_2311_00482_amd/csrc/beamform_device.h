@@ -354,7 +354,9 @@ __device__ __forceinline__ ff uniform(ff v) { return {uniform(v.hi), uniform(v.l
 
 enum Group : int { kGroups = 0, kOneGroup = 1, kShared = 2 };
 
-constexpr int kIqAhead = 4;  // IQ modes: window entries of a pixel read ahead
+// IQ modes: window entries of a pixel read ahead. Predicated kernels: one at a time,
+// in as many registers as their sums leave.
+constexpr int iq_ahead(int, bool pred) { return pred ? 1 : 4; }
 
 // a compile-time flag handed to the generic lambdas of the channel loop
 template <bool B> struct Flag { static constexpr bool value = B; };
@@ -677,24 +679,25 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
         const float rho = P.iq_r * rxl;
         const float cr = __builtin_amdgcn_cosf(rho), sr = __builtin_amdgcn_sinf(rho);
         const float Rx = w * (pk.x * cr - pk.y * sr), Ry = w * (pk.x * sr + pk.y * cr);
-        // kIqAhead angles' entries are read before the first is used: left alone,
+        // AHEAD angles' entries are read before the first is used: left alone,
         // the compiler reads one entry at a time (all eleven angles' entries
         // would take 44 registers beside 33 of sums and transmit delays)
+        constexpr int AHEAD = iq_ahead(AM, PRED);
 #pragma unroll
-        for (int g = 0; g < AM; g += kIqAhead) {
-          float sv[kIqAhead];
-          float4 qv[kIqAhead];
+        for (int g = 0; g < AM; g += AHEAD) {
+          float sv[AHEAD];
+          float4 qv[AHEAD];
 #pragma unroll
-          for (int i = 0; i < kIqAhead; ++i) {
+          for (int i = 0; i < AHEAD; ++i) {
             const int a = g + i;
             if (a < AM && (!PRED || a < A)) {
               sv[i] = txl[a < AM ? a : 0] + rxl;
               qv[i] = *(const float4 *)(wb + a * wstride + (floor_i32(sv[i]) << 4));
             }
           }
-          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (AHEAD > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int i = 0; i < kIqAhead; ++i) {
+          for (int i = 0; i < AHEAD; ++i) {
             const int a = g + i;
             if (a < AM && (!PRED || a < A)) {
               const float4 q = qv[i];

@@ -21,12 +21,21 @@ namespace {
 // blocks per CU, as many as the default LDS budget holds, up to 16 angles (IQ:
 // 11, two sums and a transmit delay each), two beyond. 11-angle 1024 x 1024
 // frames: IQ-DAS 222 -> 185 us and BB-DMAS 311 -> 277 us at 80 registers (six
-// wavefronts, the entries read kIqAhead at a time) instead of 108 (four).
-constexpr int min_waves(int am, int mode) { return am <= (is_iq_mode(mode) ? 11 : 16) ? 6 : 4; }
+// wavefronts, the entries read four at a time) instead of 108 (four), with up to
+// 40 bytes a lane spilled outside the gather loop. IQ kernels of several lane
+// groups, whose addresses differ by lane, would spill in the loop from five angles
+// on: those get 128 registers (11 angles, 512 x 512 pixels of 128 channels, two
+// groups: IQ-DAS 82 us, 111 at 80 registers, 98 without a bound). The predicated
+// IQ kernels hold 64 sums and 32 transmit delays and get 256 (17 angles on 384 x
+// 384 pixels 173 us at 165 registers, 1006 at 128 with 696 bytes spilled).
+constexpr int min_waves(int am, bool pred, int mode, int group) {
+  if (is_iq_mode(mode)) return pred ? 2 : (am <= (group == dev::kGroups ? 4 : 11) ? 6 : 4);
+  return am <= 16 ? 6 : 4;
+}
 
 template <int AM, bool PRED, int MODE, int GROUP>
 __global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
-    __attribute__((amdgpu_waves_per_eu(min_waves(AM, MODE)))) k_beamform(const FramePlan P) {
+    __attribute__((amdgpu_waves_per_eu(min_waves(AM, PRED, MODE, GROUP)))) k_beamform(const FramePlan P) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
   // RF modes: clear the frame maximum the post-processing folds into (the IQ
