@@ -18,9 +18,14 @@ namespace pwbf {
 namespace {
 
 // Wavefronts per SIMD the register allocation leaves room for: three 8-wavefront
-// blocks per CU, as many as the default LDS budget holds, up to 16 angles (IQ:
-// 11, two sums and a transmit delay each), two beyond. 11-angle 1024 x 1024
-// frames: IQ-DAS 222 -> 185 us and BB-DMAS 311 -> 277 us at 80 registers (six
+// blocks per CU, as many as the default LDS budget holds, where the unrolled angles
+// fit 80 registers without being read one after another, two beyond. DAS: up to 12
+// angles, 8 in several lane groups (512 x 512 pixels of 128 channels in 16 x 32
+// tiles, 16 angles: 66 us at 95 registers, 89 at 80; 11 angles in four groups 81 and
+// 91). DMAS and pDAS: up to 12 (14 angles 85 and 92 us), in several lane groups to 16
+// (14 angles 106 and 90 us), except that blocks of four wavefronts or fewer cannot
+// fill the registers so (133 and 142 us). IQ: up to 11 (two sums and a transmit delay
+// each). 11-angle 1024 x 1024 frames: IQ-DAS 222 -> 185 us and BB-DMAS 311 -> 277 us at 80 registers (six
 // wavefronts, the entries read four at a time) instead of 108 (four), with up to
 // 40 bytes a lane spilled outside the gather loop. IQ kernels of several lane
 // groups, whose addresses differ by lane, would spill in the loop from five angles
@@ -30,12 +35,13 @@ namespace {
 // 384 pixels 173 us at 165 registers, 1006 at 128 with 696 bytes spilled).
 constexpr int min_waves(int am, bool pred, int mode, int group) {
   if (is_iq_mode(mode)) return pred ? 2 : (am <= (group == dev::kGroups ? 4 : 11) ? 6 : 4);
-  return am <= 16 ? 6 : 4;
+  if (mode == kDas) return am <= (group == dev::kGroups ? 8 : 12) ? 6 : 4;
+  return am <= (group == dev::kGroups ? 16 : 12) ? 6 : 4;
 }
 
-template <int AM, bool PRED, int MODE, int GROUP>
+template <int AM, bool PRED, int MODE, int GROUP, int WAVES = min_waves(AM, PRED, MODE, GROUP)>
 __global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
-    __attribute__((amdgpu_waves_per_eu(min_waves(AM, PRED, MODE, GROUP)))) k_beamform(const FramePlan P) {
+    __attribute__((amdgpu_waves_per_eu(WAVES))) k_beamform(const FramePlan P) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
   // RF modes: clear the frame maximum the post-processing folds into (the IQ
@@ -51,6 +57,13 @@ hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
   const dim3 block(kWave * P.wz * P.wx * P.wc);
   const dim3 grid(P.n_tiles);
   const size_t lds = plan_lds_bytes(P);
+  if constexpr (wave_ref_mode(MODE) && AM > 11 && AM <= 16) {
+    if (P.cpw > 1 && P.wz * P.wx <= 4) {  // four wavefronts: see min_waves
+      hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups, 4>), grid, block, lds, stream,
+                         P);
+      return hipGetLastError();
+    }
+  }
   if (P.cpw > 1)
     hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups>), grid, block, lds, stream, P);
   else if (P.wc > 1)
