@@ -17,25 +17,28 @@ namespace pwbf {
 
 namespace {
 
-// Wavefronts per SIMD the register allocation leaves room for: three 8-wavefront
-// blocks per CU, as many as the default LDS budget holds, where the unrolled angles
-// fit 80 registers without being read one after another, two beyond. DAS: up to 12
-// angles, 8 in several lane groups (512 x 512 pixels of 128 channels in 16 x 32
-// tiles, 16 angles: 66 us at 95 registers, 89 at 80; 11 angles in four groups 81 and
-// 91). DMAS and pDAS: up to 12 (14 angles 85 and 92 us), in several lane groups to 16
-// (14 angles 106 and 90 us), except that blocks of four wavefronts or fewer cannot
-// fill the registers so (133 and 142 us). IQ: up to 11 (two sums and a transmit delay
-// each). 11-angle 1024 x 1024 frames: IQ-DAS 222 -> 185 us and BB-DMAS 311 -> 277 us at 80 registers (six
-// wavefronts, the entries read four at a time) instead of 108 (four), with up to
-// 40 bytes a lane spilled outside the gather loop. IQ kernels of several lane
-// groups, whose addresses differ by lane, would spill in the loop from five angles
-// on: those get 128 registers (11 angles, 512 x 512 pixels of 128 channels, two
-// groups: IQ-DAS 82 us, 111 at 80 registers, 98 without a bound). The predicated
-// IQ kernels hold 64 sums and 32 transmit delays and get 256 (17 angles on 384 x
-// 384 pixels 173 us at 165 registers, 1006 at 128 with 696 bytes spilled).
+// Wavefronts per SIMD the register allocation leaves room for: six (80 registers), so
+// that three 8-wavefront blocks fit a CU as the default LDS budget lets them, where the
+// unrolled angles fit without being read one after another; else four (128).
+//   DAS: six up to 11 angles, 8 in several lane groups (512 x 512 pixels of 128
+//   channels, 16 x 32 tiles, 16 angles: 66 us at 95 registers, 89 at 80; 11 angles in
+//   four groups 81 and 91), and for 13 to 16 angles of wavefronts that share pixels
+//   where the launch fills those three blocks twice (16 angles of 128 channels, 1000 x
+//   1000: 178 us at 80 registers, 194 at 128; 384 x 384: 43 and 34).
+//   DMAS, pDAS: six up to 12 (14-angle DMAS 85 us at 115 registers, 92 at 80), in
+//   several lane groups up to 16 (106 and 90), except that blocks of four wavefronts
+//   or fewer cannot fill the registers so (133 and 142).
+//   IQ: six up to 11, two sums and a transmit delay each (1024 x 1024 IQ-DAS 222 us at
+//   108 registers, 185 at 80 with the entries read four at a time; BB-DMAS 311 and
+//   277), with up to 40 bytes a lane spilled outside the gather loop. In several lane
+//   groups, whose addresses differ by lane, the loop itself would spill from five
+//   angles on: four (11 angles, 512 x 512, two groups: 82 us, 111 at 80 registers, 98
+//   without a bound). The predicated kernels hold 64 sums and 32 transmit delays and
+//   get 256 registers (17 angles, 384 x 384, 173 us at 165 registers, 1006 at 128 with
+//   696 bytes spilled).
 constexpr int min_waves(int am, bool pred, int mode, int group) {
   if (is_iq_mode(mode)) return pred ? 2 : (am <= (group == dev::kGroups ? 4 : 11) ? 6 : 4);
-  if (mode == kDas) return am <= (group == dev::kGroups ? 8 : 12) ? 6 : 4;
+  if (mode == kDas) return am <= (group == dev::kGroups ? 8 : 11) ? 6 : 4;
   return am <= (group == dev::kGroups ? 16 : 12) ? 6 : 4;
 }
 
@@ -60,6 +63,13 @@ hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
   if constexpr (wave_ref_mode(MODE) && AM > 11 && AM <= 16) {
     if (P.cpw > 1 && P.wz * P.wx <= 4) {  // four wavefronts: see min_waves
       hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups, 4>), grid, block, lds, stream,
+                         P);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (MODE == kDas && AM > 12 && AM <= 16) {
+    if (P.cpw == 1 && P.wc > 1 && P.n_tiles >= 2 * 3 * 256) {  // see min_waves
+      hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kShared, 6>), grid, block, lds, stream,
                          P);
       return hipGetLastError();
     }
