@@ -173,14 +173,12 @@ int validate_outputs(const pwbf_geometry *g, const pwbf_outputs *o, void *ws, si
   return PWBF_OK;
 }
 
-// Default launch shape. Tiles are 16 pixels deep: the LDS window of a tile
-// grows as ~2 DZ TZ + DX (1 + |sin|) TX samples, which for a fixed pixel count
-// is smallest near TZ = 16 on the usual grids (dz ~ dx), and shallow tiles keep
-// the per-pixel delay offsets small, which keeps float32 delays accurate. A
-// wavefront covers 8 x 8 pixels (2 x 4 wavefronts per 16 x 32 tile): its lanes'
-// delays then span fewer window entries per gather than a 16 x 4 column
-// layout (~10% faster with an earlier kernel; with the current one the two
-// shapes time within 0.5% on every benchmark workload). Small frames split channels
+// Default launch shape of batch and serving frames, of root-mode single frames and of
+// single frames of a million pixels or more; also what completes an explicit shape's
+// zero fields. Tiles are 16 pixels deep: the LDS window of a tile grows as
+// ~2 DZ TZ + DX (1 + |sin|) TX samples, which for a fixed pixel count is smallest near
+// TZ = 16 on the usual grids (dz ~ dx), and shallow tiles keep the per-pixel delay
+// offsets small, which keeps float32 delays accurate. Small frames split channels
 // across lane groups so there are enough waves.
 pwbf_tile default_tile(const pwbf_geometry *g) {
   pwbf_tile t;
@@ -191,8 +189,7 @@ pwbf_tile default_tile(const pwbf_geometry *g) {
   // tile's width): from a million pixels on, 4 x 2 wavefronts (a tile 32
   // pixels deep and 16 wide; on the 11-angle 1024 x 1024 frame 4-6% faster
   // than 16 x 32: DAS 104 against 110 us, pDAS 215 against 225 us); below,
-  // 2 x 2 (16 x 16, twice the blocks; on the 512 x 512 frame 3-5% faster than
-  // 32 x 16: DMAS 17.2 against 17.9 us, DAS 14.8 against 15.4 us).
+  // 2 x 2 (16 x 16, twice the blocks).
   t.lz = t.cpw == 1 ? 8 : 16;
   t.wz = t.cpw == 1 ? (pixels >= 1024 * 1024 ? 4 : 2) : 1;
   t.wx = t.cpw == 1 ? 2 : 8;
@@ -200,52 +197,103 @@ pwbf_tile default_tile(const pwbf_geometry *g) {
   return t;
 }
 
-// Wavefronts of a single frame's launch, up to which those of a tile are doubled
-// by sharing its pixels' channels (wc). One or two angles are bound by latency: a
-// wavefront that shares a pixel's channels halves its chain of LDS round trips
-// (256 x 512 DAS of 64 channels 10.0 -> 7.7 us at two per pixel, 8.3 and more at
-// four; 128 x 256 6.6 -> 6.0; a 58 x 26 preview 9.9 -> 5.0). From three angles
-// on the windows in LDS limit the blocks of a CU, and sharing puts more
-// wavefronts on each.
-static int64_t wave_target(int n_angles, int mode) {
-  return n_angles >= 3 && !is_iq_mode(mode) ? 8200 : 4500;
-}
-static int max_share(int mode) {  // each wavefront of a root mode fills a table of its own
-  return wave_ref_mode(mode) ? 4 : 8;
+// Most wavefronts of a single frame's launch at which `share` of them take a pixel's
+// channels together. Sharing shortens a wavefront's chain of LDS round trips, which
+// bounds a launch that leaves the chip partly idle, and costs a staging of the same
+// windows by more threads, which bounds one that fills it; few channels leave nothing
+// to share. The limits lie between the measured sizes at which one side turns to the
+// other, of DAS and IQ-DAS frames from 24 x 40 to 1000 x 1000 pixels of 16 to 192
+// channels and 1 to 32 angles (us, us alone, and of the default without sharing):
+//   one or two angles  128 x 128, 128 ch: 8 share 5.2 (4 share 5.7, none 5.9); 130 x
+//                      150: 4 share 5.8 (8: 6.3); 300 x 300: 2 share 7.3 (none 9.1);
+//                      512 x 400, 64 ch: none 9.3 (2 share 10.1)
+//   more (DAS)         11 angles, 128 ch, 128 x 256: 8 share 11.9 (4: 16, none 17.7);
+//                      300 x 300: 4 share 15.8 (2: 20.3, none 22.3); 384 x 384: 2
+//                      share 23.9 (4: 25.5, none 27.8). 3 angles, 16 ch, 200 x 250: 2
+//                      share 6.1 (8: 9.6), 300 x 400: none 7.2 (4: 9.8)
+//   more (IQ)          5 angles, 128 ch, 130 x 150: 4 share 12.7 (none 15.7); 32 ch,
+//                      128 x 256: none 10.8 (4: 12.1), 24 x 40: 8 share 10.2 (11.6)
+// The root modes' wavefronts each fill a table of their own reference delays, which
+// sharing repeats: 1-angle DMAS, 512 x 512, 16 ch: none 8.9 us, two 12.3; 7 angles of
+// 39 channels, 64 x 96: 4 share 9.5 (none 11.0).
+static int64_t share_limit(int share, int mode, int n_angles, int channels) {
+  const bool few = n_angles <= 2;
+  if (wave_ref_mode(mode)) return share <= 4 ? 2048 : 0;
+  if (is_iq_mode(mode) && !few) {
+    if (n_angles > 16 || channels < 32 || share == 2) return 0;
+    return share == 4 && channels >= (n_angles <= 8 ? 64 : 96) ? 2048 : 320;
+  }
+  switch (share) {
+    case 8: return few || channels < 64 ? 2048 : 4096;
+    case 4:
+      if (few) return channels < 96 ? 2048 : 4096;
+      if (channels < (n_angles > 12 ? 48 : 32)) return 2048;
+      return n_angles >= 8 && channels >= 64 ? 7680 : 6144;
+    default:
+      if (few && is_iq_mode(mode)) return channels < 64 ? 3000 : 4000;
+      if (few) return channels < 24 ? 3000 : (channels < 64 ? 4000 : 5120);
+      return channels < 32 && n_angles < 9 ? 2048 : 5120;
+  }
 }
 
-// The default shape of a single frame: tiles 16 pixels deep of 16 x 4-pixel
-// wavefronts, the fewer of them the more wavefronts are to share their channels;
-// 2 x 2 of 8 x 8 where none do, and from a million pixels on the shape of
-// default_tile.
+// The largest number of wavefronts that may share a pixel's channels in a launch of
+// `launch` wavefronts of pixels in blocks of `waves`, two channels or more for each
+// lane group (root modes: of up to four; 16-angle DMAS of 64 channels, 24 x 40, takes
+// 16.3 us in 16 lane groups, 17.6 with two sharing).
+static int most_share(int mode, int n_angles, int channels, int cpw, int64_t launch, int waves) {
+  for (int share = 8; share > 1; share /= 2)
+    if (waves * share <= kMaxWavesPerBlock && channels >= cpw * share * 2 &&
+        (cpw <= 4 || !wave_ref_mode(mode)) && launch * share <= share_limit(share, mode, n_angles, channels))
+      return share;
+  return 1;
+}
+
+// The default shape of a single frame: tiles 16 pixels deep of 16 x 4-pixel wavefronts,
+// the fewer of them the more wavefronts share their channels (share_limit, whose limits
+// were measured with these tiles); lane groups or 2 x 2 wavefronts of 8 x 8 pixels where
+// none do.
 static pwbf_tile single_tile(const pwbf_geometry *g, int n_angles, int mode) {
-  const int64_t pixels = (int64_t)g->nx * g->nz;
-  if (pixels >= 1024 * 1024) return default_tile(g);
-  const int64_t waves = (pixels + kWave - 1) / kWave, target = wave_target(n_angles, mode);
-  if (waves * 8 <= target && max_share(mode) >= 8) return {1, 16, 1, 1, 0};
-  if (waves * 4 <= target) return {1, 16, 1, 2, 0};
-  if (n_angles >= 3 && !is_iq_mode(mode)) return {1, 16, 1, 4, 0};
-  if (waves * 2 <= target) return {1, 16, 1, 2, 0};
-  return {1, 8, 2, 2, 0};
+  const int64_t pixels = (int64_t)g->nx * g->nz, waves = (pixels + kWave - 1) / kWave;
+  const pwbf_tile base = default_tile(g), square = {1, 8, 2, 2, 0};
+  const int ch = g->n_channels;
+  const bool few = n_angles <= 2;
+  if (pixels >= 1024 * 1024) return base;
+  // root modes: one lane group already from half of default_tile's size on (1-angle
+  // DMAS, 384 x 384 pixels of 16 channels 7.6 us, 10.7 in two groups)
+  if (wave_ref_mode(mode)) return waves > 2048 ? square : base;
+  auto shared = [&](int share, int wx) {
+    return most_share(mode, n_angles, ch, 1, waves, wx) >= share;
+  };
+  if (is_iq_mode(mode)) {
+    if (few) {
+      if (ch >= 32 && waves <= 512) return {1, 16, 1, 1, 0};
+      if (ch >= 32 && waves <= 1536) return {1, 16, 1, 2, 0};
+      return ch < 32 && waves <= 512 ? base : square;
+    }
+    if (shared(4, 1)) return {1, 16, 1, 1, 0};
+    return waves > (ch >= 48 ? 2560 : 1536) ? square : base;
+  }
+  if (shared(8, 1)) return {1, 16, 1, 1, 0};
+  if (shared(4, 2)) return {1, 16, 1, 2, 0};
+  if (!few) return {1, 16, 1, 4, 0};
+  if (ch >= 32 && waves <= 1700) return {1, 16, 1, 2, 0};
+  return square;
 }
 
-// How many wavefronts share a pixel's channels: as many as keep the launch within
-// wave_target, the block within 8 wavefronts, two channels or more for each lane
-// group, and their sums within the LDS. Tiles of four wavefronts whose windows
-// leave room for few blocks per CU take two whatever the launch (11-angle
-// 700 x 512 DAS of 128 channels 77 -> 55 us, 5-angle 512 x 512 32 -> 26.7; IQ
-// frames, bound by their registers, are slower with it).
+// How many wavefronts share a pixel's channels in a single-frame launch of plan P: as
+// many as share_limit allows, with their sums within the LDS. Tiles of four wavefronts
+// whose windows leave room for three blocks per CU (40 KB of its 160 and more) take two
+// whatever the launch (11-angle 700 x 512 DAS of 128 channels 77 -> 55 us, 5-angle 512 x
+// 512 32 -> 26.7; with 37 KB, 3 angles of 48 channels 13.4 -> 15.1), unless there are few
+// channels for many angles, whose registers leave room for no more wavefronts (14 angles
+// of 16 channels, 800 x 700, 38 -> 43). IQ frames, bound by their registers, and root
+// modes are slower with it.
 int choose_share(const FramePlan &P) {
   const int waves = P.wz * P.wx;
-  const int64_t launch = (int64_t)P.n_tiles * waves;
-  int wc = 1;
-  while (wc * 2 <= max_share(P.mode) && waves * wc * 2 <= kMaxWavesPerBlock &&
-         launch * wc * 2 <= wave_target(P.n_angles, P.mode) &&
-         P.n_channels >= P.cpw * wc * 4)
-    wc *= 2;
+  int wc = most_share(P.mode, P.n_angles, P.n_channels, P.cpw, (int64_t)P.n_tiles * waves, waves);
   FramePlan Q = P;
-  if (wc == 1 && waves == 4 && P.n_angles >= 3 && !is_iq_mode(P.mode) &&
-      P.n_channels >= P.cpw * 4 && 3 * plan_lds_bytes(P) > 2 * (size_t)kDefaultLdsBytes)
+  if (wc == 1 && waves == 4 && P.n_angles >= 3 && P.mode == kDas &&
+      P.n_channels >= (P.n_angles > 12 ? 32 : P.cpw * 4) && plan_lds_bytes(P) > 40 * 1024)
     wc = 2;
   for (; wc > 1; wc /= 2) {
     Q.wc = wc;
@@ -515,37 +563,57 @@ static int plan_frame_uncached(const pwbf_geometry *g, int dtype, int mode, int 
       pwbf_tile best = {0, 0, 0, 0, 0};
       int best_px = 0, best_win = 0;
       bool best_compact = false;
-      // (a single frame: no more pixels per tile than its default, whose size
-      // leaves it enough blocks)
-      const int px_max = waves ? kWave * kMaxWavesPerBlock : kWave * d.wz * d.wx;
-      for (int cpw = d.cpw; cpw <= 16; cpw *= 2) {
-        // and few enough wavefronts that as many can share its pixels' channels
-        // as the launch has room for
-        const int64_t launch = ((int64_t)g->nx * g->nz * cpw + kWave - 1) / kWave;
-        int share = 1;
-        while (!waves && share * 2 <= max_share(mode) &&
-               launch * share * 2 <= wave_target(na, mode))
-          share *= 2;
-        for (int lz = 1; lz <= kWave / cpw; lz *= 2)
-          for (const auto &wa : kArr) {
-            if (waves ? wa[0] * wa[1] != waves : wa[0] * wa[1] * share > kMaxWavesPerBlock)
-              continue;
-            const pwbf_tile t = {cpw, lz, wa[0], wa[1], 0};
-            FramePlan Q = *P;
-            std::string e2;
-            if (fit_tile(g, t, &Q, &e2) != PWBF_OK) continue;
-            const int px = std::min(Q.tile_z, g->nz) * std::min(Q.tile_x, g->nx);
-            if (px > px_max) continue;
-            const bool compact = root_compact(g, Q);
-            if ((compact && !best_compact) ||
-                (compact == best_compact &&
-                 (px > best_px || (px == best_px && Q.win < best_win)))) {
-              best = t;
-              best_px = px;
-              best_win = Q.win;
-              best_compact = compact;
+      // shapes of lane groups from cpw0 to cpw1 and at most px_max pixels; sharing:
+      // and few enough wavefronts that as many can share its pixels' channels as the
+      // launch has room for
+      auto search = [&](int cpw0, int cpw1, int px_max, bool sharing) {
+        for (int cpw = cpw0; cpw <= cpw1; cpw *= 2) {
+          const int64_t launch = ((int64_t)g->nx * g->nz * cpw + kWave - 1) / kWave;
+          const int share = sharing ? most_share(mode, na, g->n_channels, cpw, launch, 1) : 1;
+          for (int lz = 1; lz <= kWave / cpw; lz *= 2)
+            for (const auto &wa : kArr) {
+              if (waves ? wa[0] * wa[1] != waves : wa[0] * wa[1] * share > kMaxWavesPerBlock)
+                continue;
+              const pwbf_tile t = {cpw, lz, wa[0], wa[1], 0};
+              FramePlan Q = *P;
+              std::string e2;
+              if (fit_tile(g, t, &Q, &e2) != PWBF_OK) continue;
+              const int px = std::min(Q.tile_z, g->nz) * std::min(Q.tile_x, g->nx);
+              if (px > px_max) continue;
+              const bool compact = root_compact(g, Q);
+              if ((compact && !best_compact) ||
+                  (compact == best_compact &&
+                   (px > best_px || (px == best_px && Q.win < best_win)))) {
+                best = t;
+                best_px = px;
+                best_win = Q.win;
+                best_compact = compact;
+              }
             }
-          }
+        }
+      };
+      const int64_t pixels = (int64_t)g->nx * g->nz;
+      const bool root = wave_ref_mode(mode);
+      if (waves || (is_iq_mode(mode) && na > 2)) {
+        // (11-angle IQ-DAS of 128 channels, 24 x 40: 30 us, 32 with small tiles)
+        search(given.cpw, 16, kWave * kMaxWavesPerBlock, false);
+      } else if (!root) {
+        // no more pixels per tile than the default, whose size leaves enough blocks
+        search(d.cpw, 16, kWave * d.wz * d.wx, true);
+      } else {
+        // Root modes: frames of up to 8192 pixels in few lane groups share; one lane
+        // group and 256 pixels where the default had them and it is not a million
+        // pixels (3-angle DMAS of 32 channels, 512 x 400: 13.9 us, 18.2 with two groups
+        // and 512); else the largest tile (5-angle DMAS of 128 channels, 128 x 128:
+        // 8 x 4 pixels 10.4 us, 8 x 2 shared 16.9)
+        if (pixels <= 8192)
+          search(1, 4, 128, true);
+        else if (d.cpw == 1 && (given.cpw > 1 || (na <= 2 && pixels < 1024 * 1024)))
+          search(1, 16, 256, false);
+        if (!best_compact) {
+          best_px = 0;
+          search(given.cpw, 16, kWave * kMaxWavesPerBlock, false);
+        }
       }
       if (best_px > 0) {
         rc_fit = fit_tile(g, best, P, err);
