@@ -113,10 +113,10 @@ constexpr int kRawBufferWord3 = 0x00020000;
 // The five samples come through wide loads (one or two instructions instead of
 // five). Where those of some thread of the wavefront straddle an end of their
 // record, or the storage is not dword-aligned, all are read one by one, clamped
-// into the record, and the outside ones replaced by zero. Every read stays inside the RF buffer. (Two or
-// four quads of a thread loaded before the first is written were slower: 103 us
-// at two for the 11-angle 1024 x 1024 DAS frame against 101.5; the other blocks
-// of the CU gather meanwhile.)
+// into the record, and the outside ones replaced by zero. Every read stays inside
+// the RF buffer. (Two or four quads of a thread loaded before the first is written
+// were slower: 103 us at two for the 11-angle 1024 x 1024 DAS frame against 101.5;
+// the other blocks of the CU gather meanwhile.)
 struct QuadWalk {
   int row0, drow, j0;
   bool active;
@@ -137,13 +137,16 @@ __device__ __forceinline__ QuadWalk quad_walk(int W4) {
 // The rows of a chunk as the staging threads address them.
 struct StageRows {
   int rows, A;     // rows of the chunk, angles
-  int e0, e_hi;    // first channel of the chunk, end of the tile's channels
+  int real;        // rows of channels of the tile; the rest are padding
+  int e0;          // first channel of the chunk
   int off;         // off_t + off_r
   const int *s_lt;  // [A] window origins of the angles
   const int *s_lr;  // window origins of the chunk's channels
 };
 
-// Row r: the element offset of its record and its window's first sample.
+// Row r: the element offset of its record and its window's first sample. Padding rows
+// read the window of the channel after the tile's (the last one again past the array),
+// so that they do not keep a wavefront from its wide loads, and are zeroed afterwards.
 // r / A through a float reciprocal when A is not known at compile time
 // (r < 2^13: (r + 0.5) / A lies at least 1 / 64 from an integer).
 template <int AK>
@@ -158,10 +161,10 @@ __device__ __forceinline__ int2 stage_row(const FramePlan &P, const StageRows &S
   // the record offset is a full 32-bit product (n_samples may exceed the 24-bit
   // multiplier's range; the host bounds the product below 2^31)
   return make_int2((__mul24(a, P.n_channels) + min(e, P.n_channels - 1)) * P.n_samples,
-                   e < S.e_hi ? S.s_lt[a] + S.s_lr[c] : -(1 << 30));
+                   S.s_lt[a] + S.s_lr[c]);
 }
 
-template <int DT, int MODE, int AK>
+template <int DT, int MODE, int AK, bool PAD>
 __device__ __forceinline__ void stage_windows(const FramePlan &P, const StageRows &S,
                                               float2 *s_pairs) {
   using R = RfT<DT>;
@@ -191,6 +194,10 @@ __device__ __forceinline__ void stage_windows(const FramePlan &P, const StageRow
         u[k] = (unsigned)i < (unsigned)Ns ? v : 0.f;
       }
     }
+    if constexpr (PAD) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) u[k] = row < S.real ? u[k] : 0.f;
+    }
     float v8[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -205,7 +212,7 @@ __device__ __forceinline__ void stage_windows(const FramePlan &P, const StageRow
 }
 
 // The IQ modes' windows from complex float32 samples.
-template <int AK>
+template <int AK, bool PAD>
 __device__ __forceinline__ void stage_windows_iq(const FramePlan &P, const StageRows &S,
                                                  float4 *s_ent) {
   const int Ns = P.n_samples, win = P.win;
@@ -246,6 +253,13 @@ __device__ __forceinline__ void stage_windows_iq(const FramePlan &P, const Stage
         const bool in = (unsigned)i < (unsigned)Ns;
         ur[k] = in ? re : 0.f;
         ui[k] = in ? im : 0.f;
+      }
+    }
+    if constexpr (PAD) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        ur[k] = row < S.real ? ur[k] : 0.f;
+        ui[k] = row < S.real ? ui[k] : 0.f;
       }
     }
     float4 *dst = s_ent + __mul24(row, win) + j0;
@@ -625,15 +639,15 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
       }
     }
     constexpr int AK = PRED ? 0 : AM;
-    const StageRows SR = {cnt_pad * A, A, e0, e_hi, P.off_t + P.off_r, s_lt, s_lr + ct};
+    const StageRows SR = {cnt_pad * A, A, cnt * A, e0, P.off_t + P.off_r, s_lt, s_lr + ct};
     if constexpr (IQ)
-      stage_windows_iq<AK>(P, SR, (float4 *)s_pairs);
+      stage_windows_iq<AK, !ONEGRP>(P, SR, (float4 *)s_pairs);
     else if (P.dtype == kI16)
-      stage_windows<kI16, MODE, AK>(P, SR, s_pairs);
+      stage_windows<kI16, MODE, AK, !ONEGRP>(P, SR, s_pairs);
     else if (P.dtype == kF16)
-      stage_windows<kF16, MODE, AK>(P, SR, s_pairs);
+      stage_windows<kF16, MODE, AK, !ONEGRP>(P, SR, s_pairs);
     else
-      stage_windows<kF32, MODE, AK>(P, SR, s_pairs);
+      stage_windows<kF32, MODE, AK, !ONEGRP>(P, SR, s_pairs);
     __syncthreads();
 
     const int wstride = win * P.entry_bytes;  // bytes between angle windows
