@@ -366,7 +366,10 @@ __device__ __forceinline__ float uniform(float v) {
 }
 __device__ __forceinline__ ff uniform(ff v) { return {uniform(v.hi), uniform(v.lo)}; }
 
-enum Group : int { kGroups = 0, kOneGroup = 1, kShared = 2 };
+// Lane groups per wavefront (one or several) and wavefronts per pixel (one or several).
+enum Group : int { kGroups = 0, kOneGroup = 1, kShared = 2, kGroupsShared = 3 };
+constexpr bool lane_groups(int group) { return group == kGroups || group == kGroupsShared; }
+constexpr bool shares_pixels(int group) { return group == kShared || group == kGroupsShared; }
 
 // IQ modes: window entries of a pixel read ahead. One or two angles: the compiler's
 // own order, which reads the second channel of an iteration ahead too (a one-angle
@@ -381,10 +384,10 @@ template <bool B> struct Flag { static constexpr bool value = B; };
 // AM: angles handled per pixel; PRED: AM is an upper bound and angles >= A are
 // skipped (17..32 angles of the IQ modes, batch and serving frames of other than
 // 1, 5 and 11 angles), else exactly AM == A angles, fully unrolled.
-// GROUP: kGroups, any lane groups per wavefront and wavefronts per pixel;
-// kOneGroup, one of each; kShared, one lane group (cpw == 1) and any wavefronts
-// per pixel (a stride of channels that the compiler does not know costs the
-// 11-angle DAS loop 15%). With one lane group the LDS window of a
+// GROUP: one lane group per wavefront (cpw == 1) or several, one wavefront per pixel
+// (wc == 1) or several. A stride of channels that the compiler does not know costs the
+// 11-angle DAS loop of one lane group 15%, and frames of several 2-6% (3-angle DMAS of
+// 128 channels, 60 x 60, 7.6 us against 7.2). With one lane group the LDS window of a
 // channel is the same for the whole wavefront and its address stays scalar.
 // SEL: the apodization weight carries the aperture test (needed for boxcar).
 //
@@ -430,8 +433,8 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform
-  constexpr bool ONEGRP = GROUP != kGroups;
-  const int cpw = ONEGRP ? 1 : P.cpw, wc = GROUP == kOneGroup ? 1 : P.wc;
+  constexpr bool ONEGRP = !lane_groups(GROUP), SHARED = shares_pixels(GROUP);
+  const int cpw = ONEGRP ? 1 : P.cpw, wc = SHARED ? P.wc : 1;
   const int ppw = kWave / cpw;  // lanes per group
   const int pl = lane & (ppw - 1), grp = ONEGRP ? 0 : lane / ppw;
   const int lz = P.lz, lx = P.lx;  // a group's pixels: lz along depth by lx along x
@@ -439,9 +442,9 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   // ((wave + 0.5) / wz lies at least 1 / 16 from an integer); lz is a power of two.
   // Wavefronts wcg = 0..wc-1 of the same pixels share their channels.
   const int nwp = P.wz * P.wx;
-  const int wcg = GROUP == kOneGroup ? 0
-                                     : __builtin_amdgcn_readfirstlane((int)(
-                                           (wave + 0.5f) * __builtin_amdgcn_rcpf((float)nwp)));
+  const int wcg = SHARED ? __builtin_amdgcn_readfirstlane(
+                               (int)((wave + 0.5f) * __builtin_amdgcn_rcpf((float)nwp)))
+                         : 0;
   const int wpix = wave - wcg * nwp;
   const int wxi = (int)((wpix + 0.5f) * __builtin_amdgcn_rcpf((float)P.wz));
   const int wzi = wpix - wxi * P.wz;
@@ -816,7 +819,6 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   // Sums over the lane groups of a wavefront, then over the wavefronts that share
   // its pixels (through the LDS of the windows, which have been read; value i of
   // plan_sums(P) values), complete in the lanes that write the pixel.
-  const bool shared = GROUP == kOneGroup ? false : wc > 1;
   float *s_sum = (float *)s_pairs;
   auto group_sum = [&](float v) __attribute__((always_inline)) {
     for (int off = ppw; off < kWave; off <<= 1) v += __shfl_xor(v, off);
@@ -826,14 +828,14 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
     s_sum[(i * nwp * wc + wave) * kWave + lane] = v;
   };
   auto get_sum = [&](int i, float v) __attribute__((always_inline)) {
-    if (shared) {
+    if constexpr (SHARED) {
       v = 0.f;
       for (int w = 0; w < wc; ++w)
         v += s_sum[(i * nwp * wc + wpix + w * nwp) * kWave + lane];
     }
     return v;
   };
-  if (shared) {
+  if constexpr (SHARED) {
     __syncthreads();
     if constexpr (MODE == kDas) {
       put_sum(0, group_sum(total));
@@ -851,7 +853,7 @@ __device__ __forceinline__ void process_tile_body(const FramePlan &P, int tz, in
   }
   // the sum of v over the lanes and wavefronts of the pixel, value i
   auto pixel_sum = [&](int i, float v) __attribute__((always_inline)) {
-    return shared ? get_sum(i, v) : group_sum(v);
+    return SHARED ? get_sum(i, v) : group_sum(v);
   };
   const bool mine = wcg == 0 && grp == 0 && ix < P.nx && iz < P.nz;
 
@@ -936,7 +938,7 @@ template <int AM, bool PRED, int MODE, int GROUP>
 __device__ __forceinline__ void process_tile(const FramePlan &P, int tz, int tx,
                                              unsigned char *smem, int hull_lo = -1,
                                              int hull_hi = -1) {
-  if constexpr ((MODE == kDas || MODE == kDmas || MODE == kPdas) && GROUP != kGroups && !PRED) {
+  if constexpr ((MODE == kDas || MODE == kDmas || MODE == kPdas) && !lane_groups(GROUP) && !PRED) {
     if (P.apod != kBoxcar) {
       process_tile_body<AM, PRED, MODE, GROUP, false>(P, tz, tx, smem, hull_lo, hull_hi);
       return;

@@ -37,9 +37,10 @@ namespace {
 //   get 256 registers (17 angles, 384 x 384, 173 us at 165 registers, 1006 at 128 with
 //   696 bytes spilled).
 constexpr int min_waves(int am, bool pred, int mode, int group) {
-  if (is_iq_mode(mode)) return pred ? 2 : (am <= (group == dev::kGroups ? 4 : 11) ? 6 : 4);
-  if (mode == kDas) return am <= (group == dev::kGroups ? 8 : 11) ? 6 : 4;
-  return am <= (group == dev::kGroups ? 16 : 12) ? 6 : 4;
+  const bool groups = dev::lane_groups(group);
+  if (is_iq_mode(mode)) return pred ? 2 : (am <= (groups ? 4 : 11) ? 6 : 4);
+  if (mode == kDas) return am <= (groups ? 8 : 11) ? 6 : 4;
+  return am <= (groups ? 16 : 12) ? 6 : 4;
 }
 
 template <int AM, bool PRED, int MODE, int GROUP, int WAVES = min_waves(AM, PRED, MODE, GROUP)>
@@ -61,7 +62,7 @@ hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
   const dim3 grid(P.n_tiles);
   const size_t lds = plan_lds_bytes(P);
   if constexpr (wave_ref_mode(MODE) && AM > 11 && AM <= 16) {
-    if (P.cpw > 1 && P.wz * P.wx <= 4) {  // four wavefronts: see min_waves
+    if (P.cpw > 1 && P.wc == 1 && P.wz * P.wx <= 4) {  // four wavefronts: see min_waves
       hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups, 4>), grid, block, lds, stream,
                          P);
       return hipGetLastError();
@@ -74,7 +75,10 @@ hipError_t launch_angles(const FramePlan &P, hipStream_t stream) {
       return hipGetLastError();
     }
   }
-  if (P.cpw > 1)
+  if (P.cpw > 1 && P.wc > 1)
+    hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroupsShared>), grid, block, lds, stream,
+                       P);
+  else if (P.cpw > 1)
     hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kGroups>), grid, block, lds, stream, P);
   else if (P.wc > 1)
     hipLaunchKernelGGL((k_beamform<AM, PRED, MODE, dev::kShared>), grid, block, lds, stream, P);

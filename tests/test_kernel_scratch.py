@@ -57,5 +57,5 @@ def scratch(tmp_path_factory):
 
 def test_sums_stay_in_registers(scratch):
     # angles, predicated, mode, lane groups, wavefronts per SIMD
-    assert len({k[:4] for k in scratch}) == 3 * (3 * 32 + 2 * 17)  # groups x (RF + IQ modes)
+    assert len({k[:4] for k in scratch}) == 4 * (3 * 32 + 2 * 17)  # groups x (RF + IQ modes)
     assert {k: v for k, v in scratch.items() if v > 64} == {}
