@@ -341,9 +341,12 @@ __global__ void __launch_bounds__(kThreads)
     r.peak = peak;
     r.ix = ix;
     r.iz = iz;
-    // lateral profile: row iz, stride nz; i and j the first pixels below half
+    // Lateral profile: row iz, stride nz; i and j the first pixels below half. A
+    // negative peak lies below its own half, so both are then the peak itself: at
+    // the image's edge a pixel that the crossing needs is missing, and the width is
+    // NaN as where a side never falls below half.
     int i = ix - reach[0], j = ix + reach[1];
-    if (i >= 0 && j < nx) {
+    if (i >= 0 && i + 1 < nx && j > 0 && j < nx) {
       const float left =
           (float)i + cross(env[(size_t)i * nz + iz], env[(size_t)(i + 1) * nz + iz], half);
       const float right =
@@ -354,7 +357,7 @@ __global__ void __launch_bounds__(kThreads)
     const float *col = env + (size_t)ix * nz;
     i = iz - reach[2];
     j = iz + reach[3];
-    if (i >= 0 && j < nz) {
+    if (i >= 0 && i + 1 < nz && j > 0 && j < nz) {
       const float left = (float)i + cross(col[i], col[i + 1], half);
       const float right = (float)(j - 1) + cross(col[j - 1], col[j], half);
       r.fwhm_z = (right - left) * dz;
