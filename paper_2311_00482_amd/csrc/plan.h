@@ -106,9 +106,6 @@ PWBF_HD constexpr bool wave_ref_mode(int mode) { return mode == kDmas || mode ==
 // (wavefront, channel) of the chunk the wavefront's reference terms and integer
 // window offset (16, DMAS and pDAS only); then the windows of the chunk.
 constexpr size_t kLdsAngleBytes = kMaxAngles * 16;
-PWBF_HD constexpr size_t lds_table_bytes(int mode) {  // per channel of the table
-  return (wave_ref_mode(mode) ? 0 : 16) + (is_iq_mode(mode) ? 8 : 0) + 4;
-}
 PWBF_HD inline size_t plan_lds_ph_offset(const FramePlan &p) {
   return kLdsAngleBytes + (wave_ref_mode(p.mode) ? 0 : (size_t)p.tab * 16);
 }
