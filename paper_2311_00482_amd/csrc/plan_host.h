@@ -24,6 +24,7 @@ pwbf_tile default_tile(const pwbf_geometry *g);
 // the wavefronts that share a pixel's channels (FramePlan::wc) in a single-frame
 // launch of plan P whose shape the library picked or the tuner found
 int choose_share(const FramePlan &P);
+void widen_table(FramePlan *P);
 // Geometry and launch shape only (no pointers). angle < 0: all angles
 // (compound); angle >= 0: that angle alone.
 // waves = 8: the batch kernel's fixed 8-wavefront blocks; 0: any 1..8.
