@@ -31,7 +31,11 @@ UNIT = "Gpixel·ch/s"
 
 # MI355X: 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz issue 3.93e13 non-packed
 # float32 lane operations per second (the packed-FP32 and FMA doublings of the
-# 157.3 TFLOP/s vector figure do not apply to this kernel's instruction mix).
+# 157.3 TFLOP/s vector figure do not apply to this kernel's instruction mix). The
+# rate is nominal, one wavefront instruction in four cycles of a SIMD: two wavefronts
+# of a SIMD have been measured to issue additions and FMAs of vector operands every
+# 2.35 cycles together and conversions, minima and shift-adds every 4.5, so a fraction
+# near one says that issue is busy, not that no faster kernel exists.
 VALU_LANE_OPS_PEAK = 256 * 4 * 16 * 2.4e9
 HBM_PEAK = 8e12
 # Algorithmic float32 operations of the beamformer (counted once, as defined):
@@ -423,8 +427,8 @@ def fk_mode(dev, torch, steps: int, warmup: int) -> dict:
     1024 x 1024 pixels): the whole call (six kernels over all angles at once,
     plus the log image), timed with HIP events around each call, with the staged
     traffic per call over the call time as an HBM fraction. That roofline does
-    not bind these calls: counter passes put them at 0.56 (Stolt) and 0.71 (Lu)
-    of the VALU issue peak over their kernels, Lu's remap at 0.87
+    not bind these calls: counter passes put them at 0.63 (Stolt) and 0.75 (Lu)
+    of the nominal VALU rate over their kernels, Lu's remap at 0.88
     (profiles/fk_c3_compound_f32.sq.md)."""
     from paper_2311_00482_amd import GeometryArg, fk_migrate, fk_workspace_bytes
     from synth import config_c3, make_frame
@@ -1024,14 +1028,15 @@ def main():
                 / (wall / args.steps) / HBM_PEAK,
                 "gather_effective_GBps": gathers * 2 * 4 / (k_ms * 1e-3) / 1e9,
                 "gather_effective_frac": gathers * 2 * 4 / (k_ms * 1e-3) / HBM_PEAK,
-                # the counters' HBM bytes over the kernel's time: why the VALU
-                # roofline, not HBM, is the binding one for this kernel
+                # the counters' HBM bytes over the kernel's time: HBM is not what
+                # binds this kernel
                 "measured_GBps": None if traffic is None else traffic / (k_ms * 1e-3) / 1e9,
                 "measured_frac": None if traffic is None else traffic / (k_ms * 1e-3) / HBM_PEAK,
-                "binding": "VALU issue: the kernel issues VALU work in every slot (SQ "
-                           "counters) while its measured HBM traffic uses a few percent "
-                           "of the peak; each RF line is staged once per tile and reread "
-                           "from LDS and L2 (85% L2 hits)"},
+                "binding": "VALU issue (110% of the nominal rate by the SQ counters) and "
+                           "LDS access (71 of its 100 us at four cycles an instruction), "
+                           "while its measured HBM traffic uses a few percent of the peak; "
+                           "each RF line is staged once per tile and reread from LDS and L2 "
+                           "(85% L2 hits)"},
         "variants": {"f16_storage": {"value": gathers * args.steps / wall16 / 1e9,
                                      "frames_per_s": args.steps / wall16,
                                      "latency_ms": {"p50": float(np.percentile(lat16, 50)),
