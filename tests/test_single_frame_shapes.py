@@ -40,10 +40,12 @@ def _plan(mode, n, channels, nx, nz, **kw):
     ("iqdas", 11, 32, 128, 256, 1),
     ("iqdas", 24, 64, 130, 150, 1),
     ("iqdas", 5, 128, 130, 150, 4),
+    ("iqdas", 11, 105, 42, 768, 1),  # the wavefronts past the grid's edge count: lane groups
 ])
 def test_sharing(mode, n, channels, nx, nz, share):
     p, got = _plan(mode, n, channels, nx, nz)
     assert got == share, p
+    assert got * p["wz"] * p["wx"] > 1, p
 
 
 @pytest.mark.parametrize("mode, n, channels, nx, nz, pixels", [
