@@ -203,7 +203,7 @@ pwbf_tile default_tile(const pwbf_geometry *g) {
 // windows by more threads, which bounds one that fills it; few channels leave nothing
 // to share. The limits lie between the measured sizes at which one side turns to the
 // other, of DAS and IQ-DAS frames from 24 x 40 to 1000 x 1000 pixels of 16 to 192
-// channels and 1 to 32 angles (us, us alone, and of the default without sharing):
+// channels and 1 to 32 angles (us, and of the default without sharing):
 //   one or two angles  128 x 128, 128 ch: 8 share 5.2 (4 share 5.7, none 5.9); 130 x
 //                      150: 4 share 5.8 (8: 6.3); 300 x 300: 2 share 7.3 (none 9.1);
 //                      512 x 400, 64 ch: none 9.3 (2 share 10.1)
@@ -212,7 +212,10 @@ pwbf_tile default_tile(const pwbf_geometry *g) {
 //                      share 23.9 (4: 25.5, none 27.8). 3 angles, 16 ch, 200 x 250: 2
 //                      share 6.1 (8: 9.6), 300 x 400: none 7.2 (4: 9.8)
 //   more (IQ)          5 angles, 128 ch, 130 x 150: 4 share 12.7 (none 15.7); 32 ch,
-//                      128 x 256: none 10.8 (4: 12.1), 24 x 40: 8 share 10.2 (11.6)
+//                      128 x 256: none 10.8 (4: 12.1), 24 x 40: 8 share 10.2 (11.6).
+//                      From 900 wavefronts on two share in one lane group where lane
+//                      groups did alone: 11 angles of 90 ch, 209 x 357: 43 (55.8); 5 of
+//                      62, 722 x 90: 12.9 (17.3); 5 of 60, 463 x 245: none 11.3 (2: 12.4)
 // The root modes' wavefronts each fill a table of their own reference delays, which
 // sharing repeats: 1-angle DMAS, 512 x 512, 16 ch: none 8.9 us, two 12.3; 7 angles of
 // 39 channels, 64 x 96: 4 share 9.5 (none 11.0).
@@ -220,7 +223,9 @@ static int64_t share_limit(int share, int mode, int n_angles, int channels) {
   const bool few = n_angles <= 2;
   if (wave_ref_mode(mode)) return share <= 4 ? 2048 : 0;
   if (is_iq_mode(mode) && !few) {
-    if (n_angles > 16 || channels < 32 || share == 2) return 0;
+    if (n_angles > 16) return 0;
+    if (share == 2) return channels < 32 ? 2600 : (channels < 48 ? 3000 : 5200);
+    if (channels < 32) return 0;
     return share == 4 && channels >= (n_angles <= 8 ? 64 : 96) ? 2048 : 320;
   }
   switch (share) {
@@ -243,7 +248,8 @@ static int64_t share_limit(int share, int mode, int n_angles, int channels) {
 static int most_share(int mode, int n_angles, int channels, int cpw, int64_t launch, int waves) {
   for (int share = 8; share > 1; share /= 2)
     if (waves * share <= kMaxWavesPerBlock && channels >= cpw * share * 2 &&
-        (cpw <= 4 || !wave_ref_mode(mode)) && launch * share <= share_limit(share, mode, n_angles, channels))
+        (cpw <= 4 || !wave_ref_mode(mode)) && (cpw == 1 || share > 2 || !is_iq_mode(mode)) &&
+        launch * share <= share_limit(share, mode, n_angles, channels))
       return share;
   return 1;
 }
@@ -262,7 +268,7 @@ static pwbf_tile single_tile(const pwbf_geometry *g, int n_angles, int mode) {
   if (pixels >= 1024 * 1024) return base;
   // root modes: one lane group already from half of default_tile's size on (1-angle
   // DMAS, 384 x 384 pixels of 16 channels 7.6 us, 10.7 in two groups)
-  if (wave_ref_mode(mode)) return waves > 2048 ? square : base;
+  if (wave_ref_mode(mode)) return waves > 1150 ? square : base;
   auto shared = [&](int share, int wx) {
     const int64_t launch = (int64_t)((g->nz + 15) / 16) * ((g->nx + 4 * wx - 1) / (4 * wx)) * wx;
     return most_share(mode, n_angles, ch, 1, launch, wx) >= share;
@@ -270,33 +276,46 @@ static pwbf_tile single_tile(const pwbf_geometry *g, int n_angles, int mode) {
   if (is_iq_mode(mode)) {
     if (few) {
       if (ch >= 32 && waves <= 512) return {1, 16, 1, 1, 0};
-      if (ch >= 32 && waves <= 1536) return {1, 16, 1, 2, 0};
-      return ch < 32 && waves <= 512 ? base : square;
+      if (ch < 32 && waves <= 512) return base;
+      return waves <= (ch >= 32 ? 1536 : 1300) ? pwbf_tile{1, 16, 1, 2, 0} : square;
     }
     if (shared(4, 1)) return {1, 16, 1, 1, 0};
-    return waves > (ch >= 48 ? 2560 : 1536) ? square : base;
+    if (n_angles > 16) return waves > (ch >= 48 ? 2560 : 1536) ? square : base;
+    if (waves <= 900) return base;
+    return waves <= 1500 ? pwbf_tile{1, 16, 1, 2, 0} : square;
   }
   if (shared(8, 1)) return {1, 16, 1, 1, 0};
   if (shared(4, 2)) return {1, 16, 1, 2, 0};
   if (!few) return {1, 16, 1, 4, 0};
-  if (ch >= 32 && waves <= 1700) return {1, 16, 1, 2, 0};
+  if (waves <= (ch >= 32 ? 1700 : 1300)) return {1, 16, 1, 2, 0};
   return square;
 }
 
 // How many wavefronts share a pixel's channels in a single-frame launch of plan P: as
-// many as share_limit allows, with their sums within the LDS. Tiles of four wavefronts
-// whose windows leave room for three blocks per CU (40 KB of its 160 and more) take two
-// whatever the launch (11-angle 700 x 512 DAS of 128 channels 77 -> 55 us, 5-angle 512 x
-// 512 32 -> 26.7; with 37 KB, 3 angles of 48 channels 13.4 -> 15.1), unless there are few
-// channels for many angles, whose registers leave room for no more wavefronts (14 angles
-// of 16 channels, 800 x 700, 38 -> 43). IQ frames, bound by their registers, and root
-// modes are slower with it.
+// many as share_limit allows, with their sums within the LDS, and whatever the launch as
+// many as a CU needs that the windows leave few blocks: four wavefronts a block from 27 KB
+// on (five blocks of its 160 KB; over 800 frames of 1 to 32 angles, one wavefront to a
+// tile 16-38% slower than two of the same tile, two 12-33% slower than four, at any number
+// of blocks; 1-angle DAS of 123 channels, 178 x 1277, 38 -> 24 us at four times), and in
+// DAS compounds eight from 40 KB on, three blocks (11-angle 700 x 512 DAS of 128 channels
+// 77 -> 55 us, 5-angle 512 x 512 32 -> 26.7; with 37 KB, 3 angles of 48 channels 13.4 ->
+// 15.1), unless there are few channels for many angles, whose registers leave room for no
+// more wavefronts (14 angles of 16 channels, 800 x 700, 38 -> 43). One or two angles from
+// four to eight: 0.85 to 1.11 of the time; IQ frames, bound by their registers, and root
+// modes are slower with eight.
 int choose_share(const FramePlan &P) {
   const int waves = P.wz * P.wx;
   int wc = most_share(P.mode, P.n_angles, P.n_channels, P.cpw, (int64_t)P.n_tiles * waves, waves);
   FramePlan Q = P;
+  const size_t lds = plan_lds_bytes(P);
+  if (P.cpw == 1 && !(is_iq_mode(P.mode) && P.n_angles > 16)) {
+    const bool eight = P.mode == kDas && P.n_angles >= 3 && lds > 40 * 1024 &&
+                       P.n_channels >= (P.n_angles > 12 ? 32 : 4);
+    const int fill = eight ? 8 : (lds > 27 * 1024 ? 4 : 1);
+    while (waves * wc * 2 <= fill && P.n_channels >= wc * 4) wc *= 2;
+  }
   if (wc == 1 && waves == 4 && P.n_angles >= 3 && P.mode == kDas &&
-      P.n_channels >= (P.n_angles > 12 ? 32 : P.cpw * 4) && plan_lds_bytes(P) > 40 * 1024)
+      P.n_channels >= (P.n_angles > 12 ? 32 : P.cpw * 4) && lds > 40 * 1024)
     wc = 2;
   for (; wc > 1; wc /= 2) {
     Q.wc = wc;

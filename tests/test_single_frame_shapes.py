@@ -40,6 +40,10 @@ def _plan(mode, n, channels, nx, nz, **kw):
     ("iqdas", 11, 32, 128, 256, 1),
     ("iqdas", 24, 64, 130, 150, 1),
     ("iqdas", 5, 128, 130, 150, 4),
+    ("iqdas", 5, 62, 722, 90, 2),   # more wavefronts than lane groups are good for
+    ("bbdmas", 11, 90, 210, 420, 2),
+    ("bbdmas", 11, 90, 500, 300, 2),
+    ("iqdas", 5, 40, 500, 300, 1),  # past them, too few channels
     ("iqdas", 11, 105, 42, 768, 1),  # the wavefronts past the grid's edge count: lane groups
 ])
 def test_sharing(mode, n, channels, nx, nz, share):
@@ -58,6 +62,54 @@ def test_root_tiles(mode, n, channels, nx, nz, pixels):
     p, share = _plan(mode, n, channels, nx, nz)
     assert share == 1
     assert 64 // p["cpw"] * p["wz"] * p["wx"] == pixels, p
+
+
+def _long_windows(nx, nz):
+    # windows that fill the LDS and leave the default tile no room
+    return geom(angles_deg=(2.0,), nx=nx, nz=nz, n_channels=121, n_samples=2400, x_min=-18e-3,
+                x_max=18e-3, z_min=8e-3, z_max=8e-3 + nz * 90e-6, f_number=1.0)
+
+
+def test_no_block_of_two_wavefronts():
+    from paper_2311_00482_amd import describe_plan
+    p = describe_plan(_long_windows(190, 900), "das", -1)
+    assert p["lds_bytes"] > 40 * 1024 and p["wz"] * p["wx"] == 2, p
+    assert p["threads_per_block"] == 4 * 64, p
+
+
+@pytest.mark.gpu
+def test_parity_long_windows():
+    import torch
+    from paper_2311_00482_amd import beamform
+    g = _long_windows(190, 900)
+    rf = rand_rf(g, 91)
+    out = beamform(g, torch.from_numpy(rf).cuda(), "das", -1, want=("rf",))
+    torch.cuda.synchronize()
+    got = out["rf"].cpu().numpy().astype(np.float64)
+    pix = np.random.default_rng(9).integers(0, g.nx * g.nz, 30000)
+    pix[:4] = [0, g.nz - 1, (g.nx - 1) * g.nz, g.nx * g.nz - 1]
+    ref = oracle.das(g, rf, -1, pix=pix, parallel=True)
+    assert np.abs(got.reshape(-1)[pix] - ref).max() <= TOL32 * np.abs(ref).max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode, n, nx, nz", [("iqdas", 5, 362, 181), ("bbdmas", 3, 402, 301)])
+def test_parity_two_share_iq(mode, n, nx, nz):
+    import torch
+    from paper_2311_00482_amd import beamform, describe_plan, iq_demodulate
+    g = geom(angles_deg=tuple(np.linspace(-8.0, 7.0, n)), nx=nx, nz=nz, n_channels=49,
+             n_samples=1024, x_min=-7e-3, x_max=7e-3, z_min=4e-3, z_max=4e-3 + nz * 50e-6,
+             f_number=1.5)
+    p = describe_plan(g, mode, -1)
+    assert p["threads_per_block"] == 2 * 64 * p["wz"] * p["wx"] and p["cpw"] == 1, p
+    rf = rand_rf(g, 92 + n)
+    iq = iq_demodulate(g, torch.from_numpy(rf).cuda())
+    out = beamform(g, iq, mode, -1, want=("rf", "imag"))
+    torch.cuda.synchronize()
+    got = out["rf"].cpu().numpy().astype(np.float64) + 1j * out["imag"].cpu().numpy()
+    ref = oracle.iq_beamform(g, oracle.iq_demodulate(g, rf.astype(np.float64)), mode, -1,
+                             parallel=True)
+    assert np.abs(got - ref).max() <= TOL32 * np.abs(ref).max()
 
 
 @pytest.mark.gpu
